@@ -176,11 +176,11 @@ arc_status arc_create(const arc_config *cfg, void *hip_stream, arc_ctx **out);
  *            out_agg [N][L] (node i's rows of Delta^(i), laid out as above),
  *            with K and L one node's row count and payload length.
  * out_idx / out_agg may be NULL only when no row is kept; otherwise they must
- * not overlap each other or grad, h, g (ARC_ERR_INVALID).  With grad, h and
- * g 16-byte aligned, d % 4 == 0 and r in {1, 2, 4, 8}, rows whose width is a
- * multiple of 4 (per tensor: tensors that also start at a multiple of 4
- * coordinates) take the vectorised path; anything else takes a slower path
- * with identical results.
+ * not overlap each other or grad, h, g (ARC_ERR_INVALID).  With r in
+ * {1, 2, 4, 8}, rows of at most 2^22 values take the vectorised path at any
+ * width and element alignment (fastest with grad, h and g 16-byte aligned and
+ * d and the widths multiples of 4); anything else takes a slower path with
+ * identical results.
  * The call returns once the work is queued on the context's stream.  On the
  * host it generates V_t (ARC_COMP_ARC; V_{t+1} is then prepared in the
  * background for the next call) into one of four pinned staging buffers

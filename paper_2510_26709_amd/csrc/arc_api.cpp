@@ -64,8 +64,8 @@ bool aligned16(const void* p) {
 bool vector_r(int32_t r) { return r == 1 || r == 2 || r == 4 || r == 8; }
 
 // Rows per group of the vectorised sketch kernels for a view of width cols,
-// or 0 when the width needs the general kernel (not a multiple of 4, or a
-// group too large for 32-bit byte offsets).  Fewer rows per group give more,
+// or 0 when the width needs the general kernel (a group too large for 32-bit
+// byte offsets).  Fewer rows per group give more,
 // shorter waves whose rows are read in longer runs (the chunk widens
 // instead): the first size whose chunk divides the width, else the one with
 // the widest chunk that fits in a row (each row's last chunk is then
@@ -81,7 +81,7 @@ bool vector_r(int32_t r) { return r == 1 || r == 2 || r == 4 || r == 8; }
 constexpr int32_t kGroupSizes[] = {8, 16, 32, 64};
 bool power_of_two(int64_t v) { return v > 0 && (v & (v - 1)) == 0; }
 int32_t vector_group_rows(int64_t cols) {
-  if (cols > (int64_t{1} << 22) || cols % 4 != 0) return 0;
+  if (cols > (int64_t{1} << 22)) return 0;
   if (power_of_two(cols) && cols >= 1024 && cols <= 4096) return 16;
   for (int32_t gr : kGroupSizes)
     if (cols % arc::vector_chunk_cols(gr) == 0) return gr;
@@ -211,12 +211,15 @@ void build_selection_plan(const std::vector<int64_t>& begin, const std::vector<i
 }
 
 struct GroupLists {
-  std::vector<arc::RowGroup> vec[4], general;  // vec: 64, 32, 16, 8 rows
+  std::vector<arc::RowGroup> vec[arc::kVecLists], general;
 };
 
-int size_slot(int32_t group_rows) {
-  return group_rows == 64 ? 0 : group_rows == 32 ? 1 : group_rows == 16 ? 2 : 3;
+// List of vectorisable groups of that many rows: 16-byte aligned rows, or any.
+int size_slot(int32_t group_rows, bool aligned) {
+  return (group_rows == 64 ? 0 : group_rows == 32 ? 1 : group_rows == 16 ? 2 : 3) +
+         (aligned ? 0 : arc::kVecLists / 2);
 }
+int32_t slot_rows(int slot) { return 64 >> slot % (arc::kVecLists / 2); }
 
 // Occupancy of one vectorised sketch launch from its groups' mean number of
 // chunks per row (weighted by coordinates).  A wave streams one chunk while
@@ -279,11 +282,12 @@ int32_t row_interleave(int64_t cols, int32_t group_rows) {
 // Row groups over `rows` rows of width `cols` that start at coordinate
 // elem_off and global row row0; the last row holds last_len <= cols values.
 // group_rows > 0: vectorisable groups of that many rows (the view has no
-// ragged row); 0: general groups of 64 rows.
+// ragged row), `aligned` where every worker's rows start on 16 bytes and end
+// there (given 16-byte aligned arrays); 0: general groups of 64 rows.
 // Vectorised groups take every S-th row of a block of S*G consecutive rows
 // (S groups per block), the rest consecutive rows.
 void add_groups(int64_t elem_off, int64_t row0, int64_t rows, int64_t cols, int64_t last_len,
-                int64_t v_off, int32_t group_rows, GroupLists* out) {
+                int64_t v_off, int32_t group_rows, bool aligned, GroupLists* out) {
   const int64_t step = group_rows > 0 ? group_rows : kGroupRows;
   auto push = [&](int64_t p, int64_t nrows, int32_t stride) {
     arc::RowGroup grp{};
@@ -294,7 +298,7 @@ void add_groups(int64_t elem_off, int64_t row0, int64_t rows, int64_t cols, int6
     grp.cols = static_cast<int32_t>(cols);
     grp.last_len = static_cast<int32_t>(p + (nrows - 1) * stride == rows - 1 ? last_len : cols);
     grp.stride = stride;
-    (group_rows > 0 ? out->vec[size_slot(group_rows)] : out->general).push_back(grp);
+    (group_rows > 0 ? out->vec[size_slot(group_rows, aligned)] : out->general).push_back(grp);
   };
   int64_t p = 0;
   const int32_t S = group_rows > 0 ? row_interleave(cols, group_rows) : 1;
@@ -338,15 +342,16 @@ void build_plan(const arc_config* cfg, arc_ctx* c) {
     c->v_off[c->n] = 0;
     c->v_floats = c->n * c->r;
     const int64_t m_full = c->d / c->n;
-    const int32_t gr = c->d % 4 == 0 && r_ok ? vector_group_rows(c->n) : 0;
+    const int32_t gr = r_ok ? vector_group_rows(c->n) : 0;
     if (gr > 0) {
-      add_groups(0, 0, m_full, c->n, c->n, 0, gr, &lists);
-      // The ragged row (a multiple of 4 values, as d and n are) is a
-      // one-row group as wide as its values.
+      const bool aligned = c->d % 4 == 0 && c->n % 4 == 0;
+      add_groups(0, 0, m_full, c->n, c->n, 0, gr, aligned, &lists);
+      // The ragged row is a one-row group as wide as its values (a multiple
+      // of 4 of them where d and n are).
       const int64_t tail = c->d - m_full * c->n;
-      if (tail > 0) add_groups(m_full * c->n, m_full, 1, tail, tail, 0, gr, &lists);
+      if (tail > 0) add_groups(m_full * c->n, m_full, 1, tail, tail, 0, gr, aligned, &lists);
     } else {
-      add_groups(0, 0, c->m, c->n, c->d - (c->m - 1) * c->n, 0, 0, &lists);
+      add_groups(0, 0, c->m, c->n, c->d - (c->m - 1) * c->n, 0, 0, false, &lists);
     }
     if (cfg->num_buckets == 0) {
       begin.push_back(c->m);
@@ -383,14 +388,15 @@ void build_plan(const arc_config* cfg, arc_ctx* c) {
       const int64_t w = cfg->tensors[b].cols;
       if (c->v_off.emplace(w, c->v_floats).second) {
         c->widths.push_back(w);
-        c->v_floats += w * c->r;
+        c->v_floats += (w * c->r + 3) / 4 * 4;  // every V_t starts on 16 bytes
       }
     }
     int64_t off = 0, row0 = 0;
     for (int32_t b = 0; b < cfg->num_tensors; ++b) {
       const arc_tensor& t = cfg->tensors[b];
-      const int32_t gr = off % 4 == 0 && c->d % 4 == 0 && r_ok ? vector_group_rows(t.cols) : 0;
-      add_groups(off, row0, t.rows, t.cols, t.cols, c->v_off[t.cols], gr, &lists);
+      const int32_t gr = r_ok ? vector_group_rows(t.cols) : 0;
+      const bool aligned = c->d % 4 == 0 && off % 4 == 0 && t.cols % 4 == 0;
+      add_groups(off, row0, t.rows, t.cols, t.cols, c->v_off[t.cols], gr, aligned, &lists);
       off += t.rows * t.cols;
       row0 += t.rows;
       begin.push_back(row0);
@@ -423,9 +429,9 @@ void build_plan(const arc_config* cfg, arc_ctx* c) {
   const int64_t nodes = c->compressor == ARC_COMP_TOPK ? c->N : 1;
   c->payload = nodes * c->payload_node;
   c->groups.clear();
-  for (int sz = 0; sz < 4; ++sz) {
+  for (int sz = 0; sz < arc::kVecLists; ++sz) {
     c->vec_count[sz] = static_cast<int64_t>(lists.vec[sz].size());
-    c->vec_occ[sz] = sketch_occupancy(lists.vec[sz], 64 >> sz);
+    c->vec_occ[sz] = sketch_occupancy(lists.vec[sz], slot_rows(sz));
     for (const arc::RowGroup& grp : lists.vec[sz])
       c->stage_elems[sz] += (grp.rows - 1) * static_cast<int64_t>(grp.cols) + grp.last_len;
     c->groups.insert(c->groups.end(), lists.vec[sz].begin(), lists.vec[sz].end());
@@ -433,7 +439,7 @@ void build_plan(const arc_config* cfg, arc_ctx* c) {
   c->nvec_groups = static_cast<int64_t>(c->groups.size());
   c->groups.insert(c->groups.end(), lists.general.begin(), lists.general.end());
   for (const arc::RowGroup& grp : lists.general)
-    c->stage_elems[4] += (grp.rows - 1) * static_cast<int64_t>(grp.cols) + grp.last_len;
+    c->stage_elems[arc::kVecLists] += (grp.rows - 1) * static_cast<int64_t>(grp.cols) + grp.last_len;
 }
 
 template <typename T>
@@ -613,8 +619,8 @@ arc_status arc_create(const arc_config* cfg, void* hip_stream, arc_ctx** out) {
     }
   }
   {
-    int launches = c->stage_elems[4] > 0 ? 1 : 0;
-    for (int sz = 0; sz < 4; ++sz) launches += c->vec_count[sz] > 0;
+    int launches = c->stage_elems[arc::kVecLists] > 0 ? 1 : 0;
+    for (int sz = 0; sz < arc::kVecLists; ++sz) launches += c->vec_count[sz] > 0;
     if (launches > 1) {
       e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking);
       for (int k = 0; k < arc::kProjectionSlots && e == hipSuccess; ++k) {
@@ -696,23 +702,22 @@ arc_status check_step_args(const arc_ctx* c, int64_t t, const void* grad, const 
 namespace {
 
 // The streaming stage (S1-S3; norm: Top-K's row norms): one launch per
-// row-group size present and one for the general groups.  When there are several, the one over the most coordinates runs on
-// the caller's stream and the others on the second stream, forked after
-// everything queued before and joined before anything queued after, so that
-// they overlap it instead of following it.
+// non-empty list of row groups.  When there are several, the one over the
+// most coordinates runs on the caller's stream and the others on the second
+// stream, forked after everything queued before and joined before anything
+// queued after, so that they overlap it instead of following it.  Without
+// `aligned` (grad, h and g on 16 bytes) the lists of aligned rows take the
+// unaligned kernels too.
 arc_status launch_streaming_stage(arc_ctx* c, const void* grad, float* h, const float* g,
-                                  int64_t nvec, int64_t ngroups, bool norm) {
-  int which[5], nl = 0, big = 0;
-  for (int sz = 0; sz < 4; ++sz)
-    if (nvec > 0 && c->vec_count[sz] > 0) which[nl++] = sz;
-  if (ngroups > nvec) which[nl++] = 4;
-  // With misaligned pointers every group is general: one launch.
-  const auto elems = [&](int w) {
-    if (w < 4) return c->stage_elems[w];
-    return nvec > 0 ? c->stage_elems[4] : c->m;  // m stands in for "all of them"
-  };
+                                  bool aligned, bool norm) {
+  constexpr int kLists = arc::kVecLists;
+  int which[kLists + 1], nl = 0, big = 0;
+  for (int sz = 0; sz < kLists; ++sz)
+    if (c->vec_count[sz] > 0) which[nl++] = sz;
+  const int64_t ngeneral = static_cast<int64_t>(c->groups.size()) - c->nvec_groups;
+  if (ngeneral > 0) which[nl++] = kLists;
   for (int l = 1; l < nl; ++l)
-    if (elems(which[l]) > elems(which[big])) big = l;
+    if (c->stage_elems[which[l]] > c->stage_elems[which[big]]) big = l;
   const bool fork = nl > 1 && c->side != nullptr;
   if (fork) {
     c->fork_slot = (c->fork_slot + 1) % arc::kProjectionSlots;
@@ -726,24 +731,26 @@ arc_status launch_streaming_stage(arc_ctx* c, const void* grad, float* h, const 
       if ((l == big) != (pass == 1)) continue;
       hipStream_t s = fork && l != big ? c->side : c->stream;
       const int w = which[l];
-      if (w == 4) {
+      if (w == kLists) {
         ARC_HIP(arc::launch_sketch_general(grad, c->grad_bf16, h, g, c->V_dev,
-                                           c->groups_dev + nvec, ngroups - nvec, c->S_dev, c->d,
-                                           c->m, c->N, norm ? 1 : c->r, c->eta, c->a, norm, s),
+                                           c->groups_dev + c->nvec_groups, ngeneral, c->S_dev,
+                                           c->d, c->m, c->N, norm ? 1 : c->r, c->eta, c->a, norm,
+                                           s),
                 norm ? "row norm launch (general rows)" : "sketch launch (general rows)");
         continue;
       }
       int64_t first = 0;
       for (int sz = 0; sz < w; ++sz) first += c->vec_count[sz];
-      const int32_t gr = 64 >> w;
+      const int32_t gr = slot_rows(w);
+      const bool unaligned = !aligned || w >= kLists / 2;
       const arc::RowGroup* grp = c->groups_dev + first;
       if (norm) {
-        ARC_HIP(arc::launch_row_norms(gr, grad, c->grad_bf16, h, g, c->V_dev, grp,
+        ARC_HIP(arc::launch_row_norms(gr, unaligned, grad, c->grad_bf16, h, g, c->V_dev, grp,
                                       c->vec_count[w], c->S_dev, c->d, c->m, c->N, c->eta, c->a,
                                       c->vec_occ[w], s),
                 "row norm launch");
       } else {
-        ARC_HIP(arc::launch_sketch_per_worker(gr, grad, c->grad_bf16, h, g, c->V_dev, grp,
+        ARC_HIP(arc::launch_sketch_per_worker(gr, unaligned, grad, c->grad_bf16, h, g, c->V_dev, grp,
                                               c->vec_count[w], c->S_dev, c->d, c->m, c->N,
                                               c->r, c->eta, c->a, c->vec_occ[w], s),
                 "sketch launch");
@@ -765,10 +772,7 @@ namespace arc {
 // payload is also added into G at the selected coordinates.
 arc_status enqueue_step(arc_ctx* c, int64_t t, const void* grad, float* h, float* g,
                         int32_t* out_idx, float* out_agg, float* G) {
-  // Vectorisable groups take the 16-byte kernels only when the three streams
-  // are 16-byte aligned; otherwise every group takes the general kernel.
-  const int64_t ngroups = static_cast<int64_t>(c->groups.size());
-  const int64_t nvec = aligned16(grad) && aligned16(h) && aligned16(g) ? c->nvec_groups : 0;
+  const bool aligned = aligned16(grad) && aligned16(h) && aligned16(g);
 
   size_t slot = 0;
   if (c->timing) {
@@ -799,7 +803,7 @@ arc_status enqueue_step(arc_ctx* c, int64_t t, const void* grad, float* h, float
     if ((st = record(c, slot, 4))) return st;
   } else if (c->compressor == ARC_COMP_TOPK) {
     // Stage 0: Eq. (11a) with every node's squared row norms of Delta.
-    if ((st = launch_streaming_stage(c, grad, h, g, nvec, ngroups, true))) return st;
+    if ((st = launch_streaming_stage(c, grad, h, g, aligned, true))) return st;
     if ((st = record(c, slot, 2))) return st;
     if ((st = record(c, slot, 3))) return st;
     // Stage 2: every node's own top-K over its norms.
@@ -835,7 +839,7 @@ arc_status enqueue_step(arc_ctx* c, int64_t t, const void* grad, float* h, float
     // workers' copies of a group in one block and summing them in LDS, for
     // every worker count: 7B with 2 workers 33.5-34.0 vs 34.4-34.7 ms, 1.1B
     // with 1 worker 2.94 vs 3.00 ms, with 2 equal.
-    if ((st = launch_streaming_stage(c, grad, h, g, nvec, ngroups, false))) return st;
+    if ((st = launch_streaming_stage(c, grad, h, g, aligned, false))) return st;
     if ((st = record(c, slot, 2))) return st;
     // Stage 1: worker sum + importance of every row.
     ARC_HIP(arc::launch_reduce_rows(c->S_dev, c->sigma_dev, c->m, c->N, c->r, c->stream),
@@ -977,20 +981,26 @@ arc_status arc_describe(const arc_ctx* c, char* buf, int64_t len) {
   for (const auto& b : c->buckets) radix += b.mode == arc::kSelectRadix;
   long long strided = 0;
   for (const auto& grp : c->groups) strided += grp.stride > 1;
+  // Group counts and launch shapes by group size, aligned rows and others.
+  long long count[4], unaligned = 0;
+  arc::SketchOccupancy occ[4];
+  for (int sz = 0; sz < 4; ++sz) {
+    count[sz] = c->vec_count[sz] + c->vec_count[4 + sz];
+    occ[sz] = c->vec_occ[c->vec_count[sz] > 0 || c->vec_count[4 + sz] == 0 ? sz : 4 + sz];
+    unaligned += c->vec_count[4 + sz];
+  }
   std::snprintf(buf, static_cast<size_t>(len),
                 "compressor=%s mode=%s sketch=%s widths=%zu row_groups=%lld vector_groups=%lld "
                 "(64:%lld 32:%lld 16:%lld 8:%lld rows) workgroup_waves=(%d%s %d%s %d%s %d%s) "
-                "interleaved_groups=%lld general_groups=%lld "
+                "interleaved_groups=%lld unaligned_groups=%lld general_groups=%lld "
                 "lds_limit=%zu buckets=%zu radix_buckets=%d select=%s%s K_total=%lld "
                 "payload=%lld",
                 comp, c->tensor_mode ? "tensors" : "single_view", sketch, c->widths.size(),
                 static_cast<long long>(ngroups), static_cast<long long>(c->nvec_groups),
-                static_cast<long long>(c->vec_count[0]), static_cast<long long>(c->vec_count[1]),
-                static_cast<long long>(c->vec_count[2]), static_cast<long long>(c->vec_count[3]),
-                c->vec_occ[0].waves, c->vec_occ[0].one_per_cu ? "/cu" : "",
-                c->vec_occ[1].waves, c->vec_occ[1].one_per_cu ? "/cu" : "",
-                c->vec_occ[2].waves, c->vec_occ[2].one_per_cu ? "/cu" : "",
-                c->vec_occ[3].waves, c->vec_occ[3].one_per_cu ? "/cu" : "", strided,
+                count[0], count[1], count[2], count[3], occ[0].waves,
+                occ[0].one_per_cu ? "/cu" : "", occ[1].waves, occ[1].one_per_cu ? "/cu" : "",
+                occ[2].waves, occ[2].one_per_cu ? "/cu" : "", occ[3].waves,
+                occ[3].one_per_cu ? "/cu" : "", strided, unaligned,
                 static_cast<long long>(ngroups - c->nvec_groups),
                 c->max_lds_per_block, c->buckets.size(),
                 radix, c->select_ws().small ? "one_workgroup_per_bucket" : "blocks:",

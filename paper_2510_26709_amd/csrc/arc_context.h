@@ -18,6 +18,9 @@
 
 namespace arc {
 
+// Lists of vectorisable row groups: four group sizes, aligned and unaligned.
+constexpr int kVecLists = 8;
+
 // HIP events recorded per step when stage timing is on.
 constexpr int kEventsPerStep = 6;
 
@@ -57,13 +60,14 @@ struct arc_ctx {
   std::vector<int64_t> widths;
   std::map<int64_t, int64_t> v_off;
   int64_t v_floats = 0;
-  // row groups: the vectorisable ones by group size (64, 32, 16, 8 rows),
-  // then the general ones
+  // row groups, one list per launch: the vectorisable ones with 16-byte
+  // aligned rows by group size (64, 32, 16, 8 rows: lists 0-3), those with
+  // any other rows by group size (lists 4-7), then the general ones
   std::vector<arc::RowGroup> groups;
   int64_t nvec_groups = 0;
-  std::array<int64_t, 4> vec_count{};  // groups of 64, 32, 16 and 8 rows
-  std::array<int64_t, 5> stage_elems{};  // coordinates per launch: those sizes, general
-  std::array<arc::SketchOccupancy, 4> vec_occ{};  // launch shape per group size
+  std::array<int64_t, arc::kVecLists> vec_count{};  // groups per vectorisable list
+  std::array<int64_t, arc::kVecLists + 1> stage_elems{};  // coordinates per list, general last
+  std::array<arc::SketchOccupancy, arc::kVecLists> vec_occ{};  // launch shape per list
   // per-tensor gather
   std::vector<arc::GatherBucket> gather;
   int64_t gather_work = 0;

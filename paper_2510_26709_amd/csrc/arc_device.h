@@ -58,6 +58,26 @@ __device__ __forceinline__ uint2 buffer_load_u2(buffer_rsrc r, uint32_t off) {
 }
 
 template <int kPolicy>
+__device__ __forceinline__ uint32_t buffer_load_u1(buffer_rsrc r, uint32_t off) {
+  return __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, kPolicy);
+}
+
+template <int kPolicy>
+__device__ __forceinline__ uint32_t buffer_load_u16(buffer_rsrc r, uint32_t off) {
+  return (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, kPolicy);
+}
+
+template <int kPolicy>
+__device__ __forceinline__ float buffer_load_f1(buffer_rsrc r, uint32_t off) {
+  return __uint_as_float(buffer_load_u1<kPolicy>(r, off));
+}
+
+template <int kPolicy>
+__device__ __forceinline__ void buffer_store_f1(buffer_rsrc r, uint32_t off, float v) {
+  __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, (int)off, 0, kPolicy);
+}
+
+template <int kPolicy>
 __device__ __forceinline__ void buffer_store_f4(buffer_rsrc r, uint32_t off, float4 v) {
   const u32x4_t w = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z),
                      __float_as_uint(v.w)};

@@ -125,9 +125,10 @@ struct SketchOccupancy {
 
 // Momentum + residual + per-worker sketch into S for the row groups
 // groups[0 .. ngroups), any N.  Every group must be vectorisable for
-// group_rows in {64, 32, 16, 8}: at most group_rows rows, cols a multiple of
-// 4 and at most 2^22, 16-byte aligned rows, r in {1, 2, 4, 8}.
-hipError_t launch_sketch_per_worker(int32_t group_rows, const void* grad, int32_t grad_bf16,
+// group_rows in {64, 32, 16, 8}: at most group_rows rows, cols at most 2^22,
+// r in {1, 2, 4, 8}; without `unaligned`, also cols a multiple of 4 and
+// 16-byte aligned rows.
+hipError_t launch_sketch_per_worker(int32_t group_rows, bool unaligned, const void* grad, int32_t grad_bf16,
                                     float* h, const float* g, const float* V,
                                     const RowGroup* groups, int64_t ngroups, float* S,
                                     int64_t d, int64_t m, int32_t N, int32_t r, float eta,
@@ -143,7 +144,7 @@ hipError_t launch_sketch_general(const void* grad, int32_t grad_bf16, float* h,
 
 // Momentum + residual + per-worker squared row norms of Delta into
 // norms[N][m] (Top-K), vectorisable groups as for launch_sketch_per_worker.
-hipError_t launch_row_norms(int32_t group_rows, const void* grad, int32_t grad_bf16, float* h,
+hipError_t launch_row_norms(int32_t group_rows, bool unaligned, const void* grad, int32_t grad_bf16, float* h,
                             const float* g, const float* V, const RowGroup* groups,
                             int64_t ngroups, float* norms, int64_t d, int64_t m, int32_t N,
                             float eta, float a, SketchOccupancy occ, hipStream_t stream);

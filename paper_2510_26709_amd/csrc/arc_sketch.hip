@@ -55,8 +55,10 @@ constexpr int slice_f4() {
   return k_split<R, G, NORM>() ? R * (GroupShape<G>::kChunkCols + 4) / 4
                                : slice_src_f4<R, G, NORM>();
 }
-template <int R, int G, bool NORM>
-constexpr int wave_lds_f4() { return kTileF4 + slice_f4<R, G, NORM>(); }
+// Unaligned rows keep the Delta of their last n % 4 columns after the slice,
+// one float4 per row.
+template <int R, int G, bool NORM, bool UNAL>
+constexpr int wave_lds_f4() { return kTileF4 + slice_f4<R, G, NORM>() + (UNAL ? G : 0); }
 // Offset whose access the hardware drops: a group spans at most 2^30 bytes
 // (64 consecutive rows of at most 2^22 binary32 values; the host keeps
 // groups of rows further apart within the same span), so 2^31, and the 2^30
@@ -77,9 +79,21 @@ constexpr uint32_t kDropOffset = 0x80000000u;
 // group of fewer than G rows (always consecutive rows, stride 1) the missing
 // rows read as zero and are not stored.
 // Lanes G..63 repeat the chains of lanes 0..G-1; the caller keeps only lanes
-// below the group's row count.  NORM (R = 1): the chain is the row's squared
+// below the group's row count.
+// UNAL: rows may start and end anywhere (an odd width, a worker base or a
+// tensor at an odd coordinate, pointers off 16 bytes).  16-byte accesses need
+// only whole words, so binary32 rows are streamed as they lie; a bf16 row
+// that starts in the upper half of a word is read as the two or three words
+// that hold each quad and shifted into place; the last n % 4 columns of every
+// row are taken one value per lane, loaded before the first chunk and chained
+// after the last.  Bound by HBM like the aligned kernel, less the lines that
+// two accesses share.  Such rows used to take one value per lane throughout:
+// step times before / after, 4 workers, per-tensor CIFAR ResNet-18 (11.2e6
+// binary32 values a worker, 2 past a multiple of 4) 1.266 / 0.309 ms; 3.0e6
+// bf16 values of 640 a row 0.199 / 0.097 ms.
+// NORM (R = 1): the chain is the row's squared
 // norm, fmaf(Delta, Delta, s), and V is unused.
-template <int R, bool BF16, int G, bool NORM = false>
+template <int R, bool BF16, int G, bool NORM, bool UNAL>
 __device__ __forceinline__ void sketch_rows(
     const void* __restrict__ grad, float* __restrict__ h,
     const float* __restrict__ g, const float* __restrict__ V, int64_t d,
@@ -96,15 +110,23 @@ __device__ __forceinline__ void sketch_rows(
   const int lane = threadIdx.x & (kWave - 1);
   const int sub = lane / kLPR;   // row within one load's rows
   const int quad = lane % kLPR;  // 16-byte column group within the chunk
-  const uint32_t n = (uint32_t)grp.cols;
+  const uint32_t pitch = (uint32_t)grp.cols;  // values from row to row
+  const uint32_t n = UNAL ? pitch & ~3u : pitch;  // columns taken as float4s
+  const uint32_t rem = UNAL ? pitch & 3u : 0u;    // columns past them
   const int32_t rows = grp.rows;
   const uint32_t rstride = (uint32_t)grp.stride;
   const int64_t wbase = (int64_t)i * d + grp.elem_off;
-  const uint32_t bytes = ((uint32_t)(rows - 1) * rstride + 1u) * n * 4u;
+  const uint32_t bytes = ((uint32_t)(rows - 1) * rstride + 1u) * pitch * 4u;
   const buffer_rsrc rh = make_buffer(h + wbase, bytes);
   const buffer_rsrc rg = make_buffer(g + wbase, bytes);
+  // Unaligned bf16: the resource starts and ends on the whole words that hold
+  // the group's first and last gradient; x_odd is 1 where the first one is
+  // the upper half of its word.
+  const uint16_t* xb = static_cast<const uint16_t*>(grad) + wbase;
+  const uint32_t x_odd =
+      UNAL && BF16 ? (uint32_t)(reinterpret_cast<uintptr_t>(xb) & 2u) / 2u : 0u;
   const buffer_rsrc rx =
-      BF16 ? make_buffer(static_cast<const uint16_t*>(grad) + wbase, bytes / 2)
+      BF16 ? make_buffer(xb - x_odd, UNAL ? (bytes / 2 + 2u * x_odd + 3u) & ~3u : bytes / 2)
            : make_buffer(static_cast<const float*>(grad) + wbase, bytes);
   V += grp.v_off;
   // Column windows on whole 128-byte lines.  Where every row of the group
@@ -124,8 +146,8 @@ __device__ __forceinline__ void sketch_rows(
   // / 0.322; at 6e7 values each alike.
   uint32_t shift = 0;
   if constexpr (G <= 16) {
-    if (rows == 1 || (rstride * n) % 32u == 0u)
-      shift = (uint32_t)(reinterpret_cast<uintptr_t>(h + wbase) & 127u) / 4u;
+    if (rows == 1 || (rstride * pitch) % 32u == 0u)
+      shift = (uint32_t)(reinterpret_cast<uintptr_t>(h + wbase) & (UNAL ? 112u : 127u)) / 4u;
     const uint32_t plain = (n + kCW - 1) / kCW;
     if ((n + shift + kCW - 1) / kCW > plain && plain < kShiftMinChunks) shift = 0;
   }
@@ -135,7 +157,7 @@ __device__ __forceinline__ void sketch_rows(
   uint32_t off[8];
 #pragma unroll
   for (int u = 0; u < 8; ++u)
-    off[u] = ((uint32_t)(u * kRPL + sub) * rstride * n + quad * 4 - shift) * 4u;
+    off[u] = ((uint32_t)(u * kRPL + sub) * rstride * pitch + quad * 4 - shift) * 4u;
 #pragma unroll
   for (int k = 0; k < R; ++k) s[k] = 0.0f;
   float s_own = 0.0f;  // (row, k) lanes: this lane's chain
@@ -189,7 +211,16 @@ __device__ __forceinline__ void sketch_rows(
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const uint32_t o = col_off(off[u], c);
-      if constexpr (BF16 && G == 64) {
+      if constexpr (BF16 && UNAL) {
+        // The word or words that hold the lane's four gradients; the third
+        // only where they start in an upper half (any other lane's offset
+        // lies beyond the resource).  Rows start at any bf16 value, so
+        // which lanes those are differs from row to row.
+        const uint32_t b = o / 2 + 2 * x_odd;
+        const uint2 w = buffer_load_u2<kCacheDefault>(rx, b & ~3u);
+        const uint32_t w2 = buffer_load_u1<kCacheDefault>(rx, b & 2u ? (b & ~3u) + 8u : kDropOffset);
+        xv[u] = make_float4(__uint_as_float(w.x), __uint_as_float(w.y), __uint_as_float(w2), 0.f);
+      } else if constexpr (BF16 && G == 64) {
         // A row's bf16 grad for two consecutive 32-column chunks is one
         // 128-byte line; both 8-byte halves are requested together on even
         // chunks, so the line is fetched once rather than once per chunk.
@@ -213,13 +244,60 @@ __device__ __forceinline__ void sketch_rows(
       gv[u] = buffer_load_f4<kCacheNonTemporal>(rg, o);
     }
   };
+  // Unaligned rows: the last rem (at most 3) columns, one value per lane:
+  // lane l takes row l % G, column n + l / G of the kRem * 64 slots.
+  constexpr int kRem = UNAL ? (3 * G + kWave - 1) / kWave : 0;
+  constexpr int kRemRegs = kRem > 0 ? kRem : 1;
+  float* rem_tile = reinterpret_cast<float*>(vslice + slice_f4<R, G, NORM>());
+  float rem_x[kRemRegs], rem_h[kRemRegs], rem_g[kRemRegs];
+  uint32_t rem_off[kRemRegs];
+  float rem_v[3];  // (row, k) lanes: this lane's V of those columns
+  if constexpr (UNAL) {
+    if (rem != 0) {
+#pragma unroll
+      for (int q = 0; q < kRem; ++q) {
+        const int slot = lane + q * kWave, row = slot & (G - 1);
+        const uint32_t e = (uint32_t)(slot / G);
+        const uint32_t o = ((uint32_t)row * rstride * pitch + n + e) * 4u;
+        rem_off[q] = row < rows && e < rem ? o : kDropOffset;
+        if constexpr (BF16)
+          rem_x[q] = __uint_as_float(buffer_load_u16<kCacheDefault>(
+                         rx, rem_off[q] / 2 + 2 * x_odd) << 16);
+        else
+          rem_x[q] = buffer_load_f1<kCacheDefault>(rx, rem_off[q]);
+        rem_h[q] = buffer_load_f1<kCacheDefault>(rh, rem_off[q]);
+        rem_g[q] = buffer_load_f1<kCacheDefault>(rg, rem_off[q]);
+      }
+      if constexpr (kSplit) {
+#pragma unroll
+        for (uint32_t e = 0; e < 3; ++e)
+          rem_v[e] = V[(n + (e < rem ? e : 0)) * R + (lane / G) % R];
+      }
+    }
+  }
   if (nchunks > 0) issue_loads(0);
+  if constexpr (UNAL) {
+    if (rem != 0) {
+#pragma unroll
+      for (int q = 0; q < kRem; ++q) {
+        const float hn = fmaf(eta, rem_x[q], a * rem_h[q]);
+        buffer_store_f1<kCacheDefault>(rh, rem_off[q], hn);
+        const int slot = lane + q * kWave;
+        if (slot / G < 4) rem_tile[(slot & (G - 1)) * 4 + slot / G] = hn - rem_g[q];
+      }
+    }
+  }
   for (uint32_t c = 0; c < nchunks; ++c) {
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       float4 x4 = xv[u];
       if constexpr (BF16) {
-        const uint32_t w0 = __float_as_uint(xv[u].x), w1 = __float_as_uint(xv[u].y);
+        uint32_t w0 = __float_as_uint(xv[u].x), w1 = __float_as_uint(xv[u].y);
+        if constexpr (UNAL) {
+          const uint32_t half = 16u * (((off[u] / 4u) + x_odd) & 1u);
+          w0 = __builtin_amdgcn_alignbit(w1, w0, half);
+          w1 = __builtin_amdgcn_alignbit(__float_as_uint(xv[u].z), w1, half);
+        }
         x4 = make_float4(bf16_lo(w0), bf16_hi(w0), bf16_lo(w1), bf16_hi(w1));
       }
       float4 hn;
@@ -299,6 +377,20 @@ __device__ __forceinline__ void sketch_rows(
     }
     wave_lds_fence();
   }
+  if constexpr (UNAL) {
+    wave_lds_fence();
+    for (uint32_t e = 0; e < rem; ++e) {
+      const float dv = rem_tile[(lane & (G - 1)) * 4 + e];
+      if constexpr (NORM) {
+        s[0] = fmaf(dv, dv, s[0]);
+      } else if constexpr (kSplit) {
+        s_own = fmaf(dv, e == 0 ? rem_v[0] : e == 1 ? rem_v[1] : rem_v[2], s_own);
+      } else {
+#pragma unroll
+        for (int k = 0; k < R; ++k) s[k] = fmaf(dv, V[(n + e) * R + k], s[k]);
+      }
+    }
+  }
   if constexpr (kSplit) {
     // Row l % G's R results, from lanes l % G + k * G.
 #pragma unroll
@@ -312,14 +404,14 @@ __device__ __forceinline__ void sketch_rows(
 // HBM traffic per element and worker: grad (4 or 2 B) + h read and write
 // (8 B) + g read (4 B).  Delta never leaves the chip.
 // ---------------------------------------------------------------------------
-template <int R, bool BF16, int G, int WAVES, bool NORM = false>
+template <int R, bool BF16, int G, int WAVES, bool NORM, bool UNAL>
 __global__ void __launch_bounds__(WAVES * kWave)
 sketch_per_worker_kernel(const void* __restrict__ grad, float* __restrict__ h,
                          const float* __restrict__ g, const float* __restrict__ V,
                          const RowGroup* __restrict__ groups, int64_t ngroups,
                          float* __restrict__ S, int64_t d, int64_t m, float eta,
                          float a, int32_t flat) {
-  __shared__ float4 tiles[WAVES][wave_lds_f4<R, G, NORM>()];
+  __shared__ float4 tiles[WAVES][wave_lds_f4<R, G, NORM, UNAL>()];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   int32_t i;   // worker
@@ -337,7 +429,7 @@ sketch_per_worker_kernel(const void* __restrict__ grad, float* __restrict__ h,
   if (gi >= ngroups) return;  // whole wave; no block barrier follows
   const RowGroup grp = groups[gi];
   float s[R];
-  sketch_rows<R, BF16, G, NORM>(grad, h, g, V, d, grp, i, eta, a, tiles[wave], s);
+  sketch_rows<R, BF16, G, NORM, UNAL>(grad, h, g, V, d, grp, i, eta, a, tiles[wave], s);
   if (lane < grp.rows) {
     float* out = S + ((int64_t)i * m + grp.row0 + (int64_t)lane * grp.stride) * R;
 #pragma unroll
@@ -351,12 +443,12 @@ sketch_per_worker_kernel(const void* __restrict__ grad, float* __restrict__ h,
 // or any other such launch) runs per compute unit.  Fewer waves streaming at
 // once keep fewer DRAM rows open at a time; on the 1.1B-parameter workload
 // two waves per compute unit moved the stage from 5.5 to 6.1 TB/s.
-template <int R, bool BF16, int G, bool NORM, int WAVES>
+template <int R, bool BF16, int G, bool NORM, bool UNAL, int WAVES>
 void launch_per_worker_waves(bool one_per_cu, const void* grad, float* h, const float* g,
                              const float* V, const RowGroup* groups, int64_t ngroups, float* S,
                              int64_t d, int64_t m, int32_t N, float eta, float a,
                              hipStream_t stream) {
-  constexpr size_t kStatic = (size_t)WAVES * wave_lds_f4<R, G, NORM>() * sizeof(float4);
+  constexpr size_t kStatic = (size_t)WAVES * wave_lds_f4<R, G, NORM, UNAL>() * sizeof(float4);
   constexpr size_t kHalf = kLdsPerCu / 2 + 1024;  // a margin past one half
   static_assert(kStatic < kHalf, "the reservation below assumes tiles under half the LDS");
   const size_t reserve = one_per_cu ? kHalf - kStatic : 0;
@@ -371,21 +463,21 @@ void launch_per_worker_waves(bool one_per_cu, const void* grad, float* h, const 
   // dimension).
   const unsigned nbx = blocks_for(ngroups, WAVES);
   const bool flat = N % 8 == 0 && (int64_t)nbx * N <= INT32_MAX;
-  hipLaunchKernelGGL((sketch_per_worker_kernel<R, BF16, G, WAVES, NORM>),
+  hipLaunchKernelGGL((sketch_per_worker_kernel<R, BF16, G, WAVES, NORM, UNAL>),
                      flat ? dim3(nbx * (unsigned)N) : dim3(nbx, (unsigned)N), dim3(WAVES * kWave),
                      reserve, stream, grad, h, g, V, groups, ngroups, S, d, m, eta, a,
                      flat ? 1 : 0);
 }
 
-template <int R, bool BF16, int G, bool NORM>
+template <int R, bool BF16, int G, bool NORM, bool UNAL>
 void launch_per_worker(const SketchOccupancy& occ, const void* grad, float* h, const float* g,
                        const float* V, const RowGroup* groups, int64_t ngroups, float* S,
                        int64_t d, int64_t m, int32_t N, float eta, float a, hipStream_t stream) {
   if (occ.waves == 2)
-    launch_per_worker_waves<R, BF16, G, NORM, 2>(occ.one_per_cu != 0, grad, h, g, V, groups,
+    launch_per_worker_waves<R, BF16, G, NORM, UNAL, 2>(occ.one_per_cu != 0, grad, h, g, V, groups,
                                                  ngroups, S, d, m, N, eta, a, stream);
   else
-    launch_per_worker_waves<R, BF16, G, NORM, 4>(occ.one_per_cu != 0, grad, h, g, V, groups,
+    launch_per_worker_waves<R, BF16, G, NORM, UNAL, 4>(occ.one_per_cu != 0, grad, h, g, V, groups,
                                                  ngroups, S, d, m, N, eta, a, stream);
 }
 
@@ -427,11 +519,16 @@ reduce_rows_kernel(const float* __restrict__ S, float* __restrict__ sigma, int64
 
 template <int R, bool BF16, int G>
 struct PerWorkerLaunch {
-  static void run(const SketchOccupancy& occ, const void* grad, float* h, const float* g,
-                  const float* V, const RowGroup* groups, int64_t ngroups, float* S, int64_t d,
-                  int64_t m, int32_t N, float eta, float a, hipStream_t stream) {
-    launch_per_worker<R, BF16, G, false>(occ, grad, h, g, V, groups, ngroups, S, d, m, N, eta,
-                                         a, stream);
+  static void run(bool unaligned, const SketchOccupancy& occ, const void* grad, float* h,
+                  const float* g, const float* V, const RowGroup* groups, int64_t ngroups,
+                  float* S, int64_t d, int64_t m, int32_t N, float eta, float a,
+                  hipStream_t stream) {
+    if (unaligned)
+      launch_per_worker<R, BF16, G, false, true>(occ, grad, h, g, V, groups, ngroups, S, d, m, N,
+                                                 eta, a, stream);
+    else
+      launch_per_worker<R, BF16, G, false, false>(occ, grad, h, g, V, groups, ngroups, S, d, m,
+                                                  N, eta, a, stream);
   }
 };
 
@@ -465,31 +562,36 @@ bool dispatch(int32_t r, bool bf16, int32_t group_rows, Args... args) {
 
 }  // namespace
 
-hipError_t launch_sketch_per_worker(int32_t group_rows, const void* grad, int32_t grad_bf16,
+hipError_t launch_sketch_per_worker(int32_t group_rows, bool unaligned, const void* grad, int32_t grad_bf16,
                                     float* h, const float* g, const float* V,
                                     const RowGroup* groups, int64_t ngroups, float* S,
                                     int64_t d, int64_t m, int32_t N, int32_t r, float eta,
                                     float a, SketchOccupancy occ, hipStream_t stream) {
   if (ngroups <= 0) return hipSuccess;
-  if (!dispatch<PerWorkerLaunch>(r, grad_bf16 != 0, group_rows, occ, grad, h, g, V, groups,
+  if (!dispatch<PerWorkerLaunch>(r, grad_bf16 != 0, group_rows, unaligned, occ, grad, h, g, V, groups,
                                  ngroups, S, d, m, N, eta, a, stream))
     return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
-hipError_t launch_row_norms(int32_t group_rows, const void* grad, int32_t grad_bf16, float* h,
+hipError_t launch_row_norms(int32_t group_rows, bool unaligned, const void* grad, int32_t grad_bf16, float* h,
                             const float* g, const float* V, const RowGroup* groups, int64_t ngroups,
                             float* norms, int64_t d, int64_t m, int32_t N, float eta, float a,
                             SketchOccupancy occ, hipStream_t stream) {
   if (ngroups <= 0) return hipSuccess;
-#define ARC_NORM_CASE(GG)                                                                    \
-  case GG:                                                                                   \
-    if (grad_bf16)                                                                           \
-      launch_per_worker<1, true, GG, true>(occ, grad, h, g, V, groups, ngroups, norms, d, m, \
-                                           N, eta, a, stream);                               \
-    else                                                                                     \
-      launch_per_worker<1, false, GG, true>(occ, grad, h, g, V, groups, ngroups, norms, d,   \
-                                            m, N, eta, a, stream);                           \
+#define ARC_NORM_RUN(GG, BB, UU)                                                              \
+  launch_per_worker<1, BB, GG, true, UU>(occ, grad, h, g, V, groups, ngroups, norms, d, m, N, \
+                                         eta, a, stream)
+#define ARC_NORM_CASE(GG)                            \
+  case GG:                                           \
+    if (grad_bf16 && unaligned)                      \
+      ARC_NORM_RUN(GG, true, true);                  \
+    else if (grad_bf16)                              \
+      ARC_NORM_RUN(GG, true, false);                 \
+    else if (unaligned)                              \
+      ARC_NORM_RUN(GG, false, true);                 \
+    else                                             \
+      ARC_NORM_RUN(GG, false, false);                \
     break;
   switch (group_rows) {
     ARC_NORM_CASE(64)
@@ -500,6 +602,7 @@ hipError_t launch_row_norms(int32_t group_rows, const void* grad, int32_t grad_b
       return hipErrorInvalidValue;
   }
 #undef ARC_NORM_CASE
+#undef ARC_NORM_RUN
   return hipGetLastError();
 }
 

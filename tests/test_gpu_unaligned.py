@@ -1,0 +1,62 @@
+"""GPU parity of rows that do not start or end on 16 bytes: widths and worker
+bases that are not multiples of 4 values, arrays offset by single elements,
+bf16 rows that start in the upper half of a word, every r of the vectorised
+kernels, the ragged tail row and Top-K's row norms, against the oracle, bit
+for bit."""
+import pytest
+import torch
+
+from parity_util import log, run_case
+from test_gpu_compare import run_compare_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+# Widths around the group sizes' chunks (32, 64, 128, 256 columns) and the
+# quads: rows of one to three values, of 1 to 3 values past a chunk or short
+# of one, of several chunks, and whole quads on an odd worker base.
+WIDTHS = [1, 2, 3, 5, 31, 33, 62, 65, 127, 129, 147, 255, 257, 259, 510, 513, 576, 1001, 1026,
+          2303, 4099]
+
+
+@pytest.mark.parametrize("n", WIDTHS)
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_parity_odd_widths(n, dtype):
+    rows = max(3, min(9000 // n, 150)) if n > 1 else 500
+    for k, (r, N, extra, mis) in enumerate([(4, 3, 1, 0), (4, 8, n // 2, 1), (8, 2, 0, 3),
+                                            (1, 2, 2, 2), (2, 3, 3, 5)]):
+        d = n * rows + extra % n
+        log(f"[unaligned] n={n} {dtype} r={r} N={N} d={d} misalign={mis}")
+        run_case(label=f"odd_{n}_{dtype}_{k}", d=d, N=N, n=n, r=r, K=rows // 7 + 1, steps=2,
+                 grad_dtype=dtype, family=1 if dtype == "bf16" else 0, misalign=mis, check_S=True)
+
+
+# Tensors on either side of a 16-byte boundary in one layout: aligned lists,
+# unaligned lists and groups of rows 4 apart side by side.
+TENSORS = [(70, 2048, 3), (64, 27, 4), (1, 10, 1), (33, 577, 2), (40, 3072, 2), (9, 3071, 1),
+           (130, 64, 9), (2, 3, 1), (129, 300, 5), (1, 1001, 1)]
+
+
+@pytest.mark.parametrize("dtype,r,mis,pad", [("f32", 4, 0, 0), ("f32", 4, 0, 1), ("bf16", 4, 0, 1),
+                                             ("bf16", 2, 1, 3), ("f32", 8, 2, 2),
+                                             ("f32", 1, 3, 0)])
+def test_tensor_parity_mixed_alignment(dtype, r, mis, pad):
+    tensors = TENSORS + [(1, 4 - sum(a * b for a, b, _ in TENSORS) % 4 + pad, 1)]
+    log(f"[unaligned] tensors {dtype} r={r} misalign={mis} pad={pad}")
+    run_case(label=f"mixed_{dtype}_{r}_{mis}_{pad}", d=sum(a * b for a, b, _ in tensors), N=3, r=r,
+             tensors=tensors, steps=2, grad_dtype=dtype, family=1 if dtype == "bf16" else 0,
+             misalign=mis, check_S=True)
+
+
+@pytest.mark.parametrize("n,dtype,mis", [(3, "f32", 0), (33, "bf16", 1), (147, "f32", 1),
+                                         (258, "bf16", 0), (1001, "f32", 2), (2050, "bf16", 1)])
+def test_topk_norms_unaligned(n, dtype, mis):
+    log(f"[unaligned] topk n={n} {dtype} misalign={mis}")
+    run_compare_case(compressor="topk", d=n * 70 + n // 2, N=3, n=n, K=6, grad_dtype=dtype,
+                     family=1 if dtype == "bf16" else 0, misalign=mis, label=f"topk_{n}_{dtype}")
