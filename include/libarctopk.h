@@ -194,7 +194,7 @@ arc_status arc_create(const arc_config *cfg, void *hip_stream, arc_ctx **out);
  * unit: while it runs, another kernel's workgroups that need more than the
  * remaining LDS wait for a compute unit to free up.  When every bucket has
  * at most 32,768 rows, the selection runs one 1024-thread workgroup per
- * bucket holding the bucket's importances in up to 143 KB of LDS.
+ * bucket holding the bucket's importances in registers.
  */
 arc_status arc_step(arc_ctx *ctx, int64_t t, const void *grad, float *h,
                     float *g, int32_t *out_idx, float *out_agg);

@@ -96,14 +96,12 @@ struct SelectWorkspace {
 
 // Buckets of at most this many rows are selected by one workgroup each, in
 // one launch for the whole step (no global histograms or block counts), with
-// the bucket's keys held in LDS (up to 132 KiB).  Against the five
+// the bucket's keys held in registers.  Against the five
 // multi-block launches, on one MI355X: 22,832 rows (ResNet-18) 9 us less a
 // step, the 201 tensors of TinyLlama-1.1B (at most 32,000 rows) 15 us less.
 constexpr int kSmallSelectThreads = 1024;
 constexpr int kSmallKeysPerThread = 32;
 constexpr int64_t kSmallBucketRows = kSmallKeysPerThread * kSmallSelectThreads;
-// LDS words that hold r keys: one word of padding after every 32 keys.
-constexpr int64_t small_key_words(int64_t r) { return r + r / 32 + 1; }
 
 // ---- launchers; each returns hipGetLastError() ----
 
