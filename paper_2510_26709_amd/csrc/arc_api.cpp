@@ -377,7 +377,6 @@ void build_plan(const arc_config* cfg, arc_ctx* c) {
       gb.rows = bd.hi - bd.lo;
       gb.cols = static_cast<int32_t>(c->n);
       gb.k = static_cast<int32_t>(bd.k);
-      gb.vec = c->n % 4 == 0 && c->d % 4 == 0;
       if (c->compressor == ARC_COMP_TOPK) c->gather.push_back(gb);
       work += bd.k * ((c->n + 3) / 4);
     }
@@ -417,7 +416,6 @@ void build_plan(const arc_config* cfg, arc_ctx* c) {
       gb.rows = t.rows;
       gb.cols = static_cast<int32_t>(t.cols);
       gb.k = static_cast<int32_t>(bd.k);
-      gb.vec = t.cols % 4 == 0 && off % 4 == 0 && agg_off % 4 == 0 && c->d % 4 == 0;
       c->gather.push_back(gb);
       agg_off += bd.k * t.cols;
       work += bd.k * ((t.cols + 3) / 4);
@@ -811,8 +809,6 @@ arc_status enqueue_step(arc_ctx* c, int64_t t, const void* grad, float* h, float
     if ((st = record(c, slot, 4))) return st;
     // Stage 3: every node's rows, unsummed (the All-Gather payload); in the
     // model step, tagged per node for the merge that follows.
-    const bool vec = c->d % 4 == 0 && c->payload_node % 4 == 0 && aligned16(h) &&
-                     aligned16(g) && aligned16(out_agg);
     const bool merge = G != nullptr && c->mark_dev != nullptr;
     if (merge && ++c->mark_stamp == 0) {
       // After 2^32 merges the stamps wrap: clear the old tags first.
@@ -822,14 +818,14 @@ arc_status enqueue_step(arc_ctx* c, int64_t t, const void* grad, float* h, float
     }
     ARC_HIP(arc::launch_topk_gather(h, g, c->sel_dev, out_idx, out_agg, c->gather_dev,
                                     static_cast<int32_t>(c->gather.size()), c->gather_work,
-                                    c->K_node, c->payload_node, c->d, c->m, c->N, vec,
+                                    c->K_node, c->payload_node, c->d, c->m, c->N,
                                     merge ? c->mark_dev : nullptr, c->mark_stamp, c->stream),
             "gather launch");
     if (merge)
       ARC_HIP(arc::launch_topk_merge(out_agg, c->sel_dev, c->mark_dev, c->mark_stamp,
                                      c->gather_dev, static_cast<int32_t>(c->gather.size()),
                                      c->gather_work, c->K_node, c->payload_node, c->d, c->m,
-                                     c->N, G, vec && aligned16(G), c->stream),
+                                     c->N, G, c->stream),
               "merge launch");
     return record(c, slot, 5);
   } else {
@@ -850,18 +846,14 @@ arc_status enqueue_step(arc_ctx* c, int64_t t, const void* grad, float* h, float
     if ((st = record(c, slot, 4))) return st;
   }
   // Stage 3: gather + worker sum + error-feedback update.
-  const bool G_ok = G == nullptr || aligned16(G);
   if (c->tensor_mode) {
-    const bool vec_ok = aligned16(h) && aligned16(g) && aligned16(out_agg) && G_ok;
     ARC_HIP(arc::launch_gather_update_tensors(h, g, out_idx, out_agg, G, c->gather_dev,
                                               static_cast<int32_t>(c->gather.size()),
-                                              c->gather_work, c->d, c->N, vec_ok, c->stream),
+                                              c->gather_work, c->d, c->N, c->stream),
             "gather launch");
   } else {
-    const bool fast_gather = c->n % 4 == 0 && c->d % 4 == 0 && aligned16(h) && aligned16(g) &&
-                             aligned16(out_agg) && G_ok;
-    ARC_HIP(arc::launch_gather_update(fast_gather, h, g, out_idx, out_agg, G, c->K_total, c->d,
-                                      c->n, c->m, c->N, c->stream),
+    ARC_HIP(arc::launch_gather_update(h, g, out_idx, out_agg, G, c->K_total, c->d, c->n, c->m,
+                                      c->N, c->stream),
             "gather launch");
   }
   if ((st = record(c, slot, 5))) return st;

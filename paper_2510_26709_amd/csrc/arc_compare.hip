@@ -97,7 +97,7 @@ topk_gather_kernel(const float* __restrict__ h, float* __restrict__ g,
                    const int32_t* __restrict__ sel, int32_t* __restrict__ out_idx,
                    float* __restrict__ agg, const GatherBucket* __restrict__ buckets,
                    int32_t nb, int64_t work, int64_t K_total, int64_t payload, int64_t d,
-                   int64_t m, int32_t N, int32_t vec, uint64_t* __restrict__ mark,
+                   int64_t m, int32_t N, uint64_t* __restrict__ mark,
                    uint32_t stamp) {
   const int64_t w_all = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (w_all >= (int64_t)N * work) return;
@@ -119,13 +119,12 @@ topk_gather_kernel(const float* __restrict__ h, float* __restrict__ g,
   const int64_t e = bk.elem_off + pr * bk.cols + col;
   const int64_t ncols = bk.cols - col < 4 ? bk.cols - col : 4;
   const int64_t at = i * d + e;
-  if (vec && bk.vec && e + 4 <= d) {
-    const float4 hv = *reinterpret_cast<const float4*>(h + at);
-    const float4 gv = *reinterpret_cast<const float4*>(g + at);
+  if (ncols == 4 && e + 4 <= d) {
+    const float4 hv = load_f4_words(h + at);
+    const float4 gv = load_f4_words(g + at);
     const float4 dl = make_float4(hv.x - gv.x, hv.y - gv.y, hv.z - gv.z, hv.w - gv.w);
-    *reinterpret_cast<float4*>(g + at) =
-        make_float4(gv.x + dl.x, gv.y + dl.y, gv.z + dl.z, gv.w + dl.w);
-    *reinterpret_cast<float4*>(out) = dl;
+    store_f4_words(g + at, make_float4(gv.x + dl.x, gv.y + dl.y, gv.z + dl.z, gv.w + dl.w));
+    store_f4_words(out, dl);
   } else {
     for (int64_t jj = 0; jj < ncols; ++jj) {
       if (e + jj >= d) {  // past d in a ragged last row
@@ -150,7 +149,7 @@ topk_merge_kernel(const float* __restrict__ agg, const int32_t* __restrict__ sel
                   const uint64_t* __restrict__ mark, uint32_t stamp,
                   const GatherBucket* __restrict__ buckets, int32_t nb, int64_t work,
                   int64_t K_total, int64_t payload, int64_t d, int64_t m, int32_t N,
-                  float* __restrict__ G, int32_t vec) {
+                  float* __restrict__ G) {
   const int64_t w_all = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (w_all >= (int64_t)N * work) return;
   const int64_t i = w_all / work, w = w_all - i * work;
@@ -164,9 +163,8 @@ topk_merge_kernel(const float* __restrict__ agg, const int32_t* __restrict__ sel
     if ((uint32_t)(mark[j * m + p] >> 32) == stamp) return;  // a lower node owns the row
   const int64_t e = bk.elem_off + pr * bk.cols + col;
   const int64_t ncols = bk.cols - col < 4 ? bk.cols - col : 4;
-  if (vec && bk.vec && e + 4 <= d) {
-    // four columns as one 16-byte access each (rows, payload slots and G
-    // 16-byte aligned)
+  if (ncols == 4 && e + 4 <= d) {
+    // four columns as one 16-byte access each
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     bool have = false;
     for (int64_t j = i; j < N; ++j) {
@@ -174,8 +172,7 @@ topk_merge_kernel(const float* __restrict__ agg, const int32_t* __restrict__ sel
       if ((uint32_t)(mv >> 32) != stamp) continue;
       const int64_t qj = (int64_t)(uint32_t)mv;
       if (qj >= bk.k) continue;  // a broken tag touches nothing
-      const float4 v = *reinterpret_cast<const float4*>(agg + j * payload + bk.agg_off +
-                                                        qj * bk.cols + col);
+      const float4 v = load_f4_words(agg + j * payload + bk.agg_off + qj * bk.cols + col);
       if (have) {
         acc.x = acc.x + v.x;
         acc.y = acc.y + v.y;
@@ -187,12 +184,8 @@ topk_merge_kernel(const float* __restrict__ agg, const int32_t* __restrict__ sel
       have = true;
     }
     if (!have) return;
-    float4 Gv = *reinterpret_cast<const float4*>(G + e);
-    Gv.x = Gv.x + acc.x;
-    Gv.y = Gv.y + acc.y;
-    Gv.z = Gv.z + acc.z;
-    Gv.w = Gv.w + acc.w;
-    *reinterpret_cast<float4*>(G + e) = Gv;
+    const float4 Gv = load_f4_words(G + e);
+    store_f4_words(G + e, make_float4(Gv.x + acc.x, Gv.y + acc.y, Gv.z + acc.z, Gv.w + acc.w));
     return;
   }
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
@@ -247,23 +240,23 @@ hipError_t launch_randk_keys(uint64_t seed, int64_t t, int64_t m, float* keys,
 hipError_t launch_topk_gather(const float* h, float* g, const int32_t* sel, int32_t* out_idx,
                               float* agg, const GatherBucket* buckets, int32_t nb,
                               int64_t work, int64_t K_total, int64_t payload, int64_t d,
-                              int64_t m, int32_t N, bool vec, uint64_t* mark, uint32_t stamp,
+                              int64_t m, int32_t N, uint64_t* mark, uint32_t stamp,
                               hipStream_t stream) {
   if (work <= 0) return hipSuccess;
   hipLaunchKernelGGL(topk_gather_kernel, dim3(blocks_for((int64_t)N * work, 256)), dim3(256), 0,
                      stream, h, g, sel, out_idx, agg, buckets, nb, work, K_total, payload, d, m,
-                     N, vec ? 1 : 0, mark, stamp);
+                     N, mark, stamp);
   return hipGetLastError();
 }
 
 hipError_t launch_topk_merge(const float* agg, const int32_t* sel, const uint64_t* mark,
                              uint32_t stamp, const GatherBucket* buckets, int32_t nb,
                              int64_t work, int64_t K_total, int64_t payload, int64_t d,
-                             int64_t m, int32_t N, float* G, bool vec, hipStream_t stream) {
+                             int64_t m, int32_t N, float* G, hipStream_t stream) {
   if (work <= 0) return hipSuccess;
   hipLaunchKernelGGL(topk_merge_kernel, dim3(blocks_for((int64_t)N * work, 256)), dim3(256), 0,
                      stream, agg, sel, mark, stamp, buckets, nb, work, K_total, payload, d, m, N,
-                     G, vec ? 1 : 0);
+                     G);
   return hipGetLastError();
 }
 

@@ -24,6 +24,21 @@ __device__ __forceinline__ void stream_store(float4* p, float4 v) {
   __builtin_nontemporal_store(w, reinterpret_cast<f32x4_t*>(p));
 }
 
+// Four values at any word: the hardware's 16-byte global accesses need no
+// more than 4-byte alignment.
+struct __attribute__((packed, aligned(4))) f4_words {
+  float x, y, z, w;
+};
+
+__device__ __forceinline__ float4 load_f4_words(const float* p) {
+  const f4_words v = *reinterpret_cast<const f4_words*>(p);
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+
+__device__ __forceinline__ void store_f4_words(float* p, float4 v) {
+  *reinterpret_cast<f4_words*>(p) = f4_words{v.x, v.y, v.z, v.w};
+}
+
 // Raw buffer resource (stride 0) over `bytes` bytes from `base`.  Vector
 // memory instructions through it are range checked by the hardware on their
 // VGPR offset: a load at an offset >= bytes returns zero and a store there is

@@ -77,8 +77,6 @@ struct GatherBucket {
   int64_t rows;      // rows of the tensor
   int32_t cols;
   int32_t k;         // rows kept
-  int32_t vec;       // 16-byte aligned rows and payload: float4 path
-  int32_t pad;
 };
 
 struct SelectWorkspace {
@@ -166,16 +164,15 @@ hipError_t launch_randk_keys(uint64_t seed, int64_t t, int64_t m, float* keys,
 hipError_t launch_topk_gather(const float* h, float* g, const int32_t* sel, int32_t* out_idx,
                               float* agg, const GatherBucket* buckets, int32_t nb,
                               int64_t work, int64_t K_total, int64_t payload, int64_t d,
-                              int64_t m, int32_t N, bool vec, uint64_t* mark, uint32_t stamp,
+                              int64_t m, int32_t N, uint64_t* mark, uint32_t stamp,
                               hipStream_t stream);
 
 // Top-K merge after the gather with the same stamp: G += the ascending-node
-// sum of the kept values of every kept coordinate.  vec: the gather's
-// 16-byte condition holds and G is 16-byte aligned.
+// sum of the kept values of every kept coordinate.
 hipError_t launch_topk_merge(const float* agg, const int32_t* sel, const uint64_t* mark,
                              uint32_t stamp, const GatherBucket* buckets, int32_t nb,
                              int64_t work, int64_t K_total, int64_t payload, int64_t d,
-                             int64_t m, int32_t N, float* G, bool vec, hipStream_t stream);
+                             int64_t m, int32_t N, float* G, hipStream_t stream);
 
 // p[0 .. n) = 0.
 hipError_t launch_zero_u64(uint64_t* p, int64_t n, hipStream_t stream);
@@ -194,8 +191,8 @@ hipError_t launch_select(const float* sigma, const SelectWorkspace& ws,
                          int32_t* out_idx, hipStream_t stream);
 
 // Gather of the selected rows, worker sum into agg, g += Delta on them, and
-// G += agg there when G is non-null (fast: G 16-byte aligned as well).
-hipError_t launch_gather_update(bool fast, const float* h, float* g,
+// G += agg there when G is non-null.
+hipError_t launch_gather_update(const float* h, float* g,
                                 const int32_t* idx, float* agg, float* G, int64_t K_total,
                                 int64_t d, int64_t n, int64_t m, int32_t N,
                                 hipStream_t stream);
@@ -205,7 +202,7 @@ hipError_t launch_gather_update_tensors(const float* h, float* g,
                                         const int32_t* idx, float* agg, float* G,
                                         const GatherBucket* buckets, int32_t nb,
                                         int64_t total_work, int64_t d, int32_t N,
-                                        bool allow_vec, hipStream_t stream);
+                                        hipStream_t stream);
 
 // Model step (arc_model.hip).  Dense step: Eq. (11a), (11b) with the identity
 // compressor, payload added into G, every coordinate (vec: 16-byte aligned

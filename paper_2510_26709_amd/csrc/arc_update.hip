@@ -11,32 +11,26 @@
 namespace arc {
 namespace {
 
-// ---------------------------------------------------------------------------
-// Thread per (selected row, 4 columns) on the vectorised path: for each worker
-// in ascending order Delta = h - g, agg += Delta, g = g + Delta.  Rows are
-// contiguous, so every access is a coalesced 16-byte access.  Columns past d
-// give agg = +0.
-// ---------------------------------------------------------------------------
-constexpr int kMaxUnrolledWorkers = 8;
+// Work item = one selected row x 4 columns (a row's last item may have
+// fewer): for each worker in ascending order Delta = h - g, agg += Delta,
+// g = g + Delta.  Bound by memory where many rows are kept and by the chain of
+// dependent reads (bucket, row, values) where few are, so the values of up to
+// kMaxUnrolledWorkers workers are requested together (8 at a time instead of
+// 4 were no faster with 8 workers, and slower with 1: 68 against 56 us on
+// per-tensor TinyLlama-1.1B, whose one worker's reads then held more
+// registers than it used).  16-byte accesses need only whole words, so rows,
+// payload and G are taken as they lie; one value a lane where they were off
+// 16 bytes, and one worker at a time, took 46.5 us on per-tensor CIFAR
+// ResNet-18 (1.1e6 values kept, 4 workers), now 19.0.
+constexpr int kMaxUnrolledWorkers = 4;
 
-__global__ void __launch_bounds__(256)
-gather_update_fast_kernel(const float* __restrict__ h, float* __restrict__ g,
-                          const int32_t* __restrict__ idx,
-                          float* __restrict__ agg, float* __restrict__ G, int64_t K_total,
-                          int64_t d, int64_t n, int64_t m, int32_t N) {
-  const int64_t per_row = n / 4;
-  const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (tid >= K_total * per_row) return;
-  const int64_t q = tid / per_row;
-  const int64_t col = (tid - q * per_row) * 4;
-  const int64_t p = idx[q];
+// The item's ncols columns at coordinate e of every worker's vector; returns
+// their worker sum, +0 in columns at or past ncols.
+__device__ __forceinline__ float4 move_columns(const float* __restrict__ h, float* __restrict__ g,
+                                               float* __restrict__ G, int64_t e, int ncols,
+                                               int64_t d, int32_t N) {
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (p < 0 || p >= m) {  // not a row: leave the state alone
-    *reinterpret_cast<float4*>(agg + q * n + col) = acc;
-    return;
-  }
-  const int64_t e = p * n + col;
-  if (e + 4 <= d) {
+  if (ncols == 4) {
     for (int32_t i0 = 0; i0 < N; i0 += kMaxUnrolledWorkers) {
       const int32_t cnt = N - i0 < kMaxUnrolledWorkers ? N - i0 : kMaxUnrolledWorkers;
       float4 hv[kMaxUnrolledWorkers], gv[kMaxUnrolledWorkers];
@@ -44,18 +38,15 @@ gather_update_fast_kernel(const float* __restrict__ h, float* __restrict__ g,
       for (int u = 0; u < kMaxUnrolledWorkers; ++u) {
         if (u < cnt) {
           const int64_t at = (int64_t)(i0 + u) * d + e;
-          hv[u] = *reinterpret_cast<const float4*>(h + at);
-          gv[u] = *reinterpret_cast<const float4*>(g + at);
+          hv[u] = load_f4_words(h + at);
+          gv[u] = load_f4_words(g + at);
         }
       }
 #pragma unroll
       for (int u = 0; u < kMaxUnrolledWorkers; ++u) {
         if (u < cnt) {
-          float4 dl;
-          dl.x = hv[u].x - gv[u].x;
-          dl.y = hv[u].y - gv[u].y;
-          dl.z = hv[u].z - gv[u].z;
-          dl.w = hv[u].w - gv[u].w;
+          const float4 dl = make_float4(hv[u].x - gv[u].x, hv[u].y - gv[u].y,
+                                        hv[u].z - gv[u].z, hv[u].w - gv[u].w);
           if (i0 + u == 0) {
             acc = dl;
           } else {
@@ -64,83 +55,94 @@ gather_update_fast_kernel(const float* __restrict__ h, float* __restrict__ g,
             acc.z = acc.z + dl.z;
             acc.w = acc.w + dl.w;
           }
-          float4 gn;
-          gn.x = gv[u].x + dl.x;
-          gn.y = gv[u].y + dl.y;
-          gn.z = gv[u].z + dl.z;
-          gn.w = gv[u].w + dl.w;
-          *reinterpret_cast<float4*>(g + (int64_t)(i0 + u) * d + e) = gn;
+          store_f4_words(g + (int64_t)(i0 + u) * d + e,
+                         make_float4(gv[u].x + dl.x, gv[u].y + dl.y, gv[u].z + dl.z,
+                                     gv[u].w + dl.w));
         }
       }
     }
     if (G) {
-      float4 Gv = *reinterpret_cast<const float4*>(G + e);
-      Gv.x = Gv.x + acc.x;
-      Gv.y = Gv.y + acc.y;
-      Gv.z = Gv.z + acc.z;
-      Gv.w = Gv.w + acc.w;
-      *reinterpret_cast<float4*>(G + e) = Gv;
+      const float4 Gv = load_f4_words(G + e);
+      store_f4_words(G + e, make_float4(Gv.x + acc.x, Gv.y + acc.y, Gv.z + acc.z, Gv.w + acc.w));
     }
   } else {
     float a4[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int jj = 0; jj < 4; ++jj) {
-      if (e + jj >= d) break;
-      for (int32_t i = 0; i < N; ++i) {
-        const int64_t at = (int64_t)i * d + e + jj;
-        const float dl = h[at] - g[at];
-        a4[jj] = (i == 0) ? dl : a4[jj] + dl;
-        g[at] = g[at] + dl;
+#pragma unroll
+    for (int jj = 0; jj < 3; ++jj) {
+      if (jj < ncols) {
+        for (int32_t i = 0; i < N; ++i) {
+          const int64_t at = (int64_t)i * d + e + jj;
+          const float dl = h[at] - g[at];
+          a4[jj] = (i == 0) ? dl : a4[jj] + dl;
+          g[at] = g[at] + dl;
+        }
+        if (G) G[e + jj] = G[e + jj] + a4[jj];
       }
-      if (G) G[e + jj] = G[e + jj] + a4[jj];
     }
-    acc = make_float4(a4[0], a4[1], a4[2], a4[3]);
+    acc = make_float4(a4[0], a4[1], a4[2], 0.f);
   }
-  *reinterpret_cast<float4*>(agg + q * n + col) = acc;
+  return acc;
 }
 
+// The first ncols of v at out.
+__device__ __forceinline__ void store_columns(float* out, float4 v, int ncols) {
+  if (ncols == 4) {
+    store_f4_words(out, v);
+  } else {
+    const float a4[3] = {v.x, v.y, v.z};
+#pragma unroll
+    for (int jj = 0; jj < 3; ++jj)
+      if (jj < ncols) out[jj] = a4[jj];
+  }
+}
+
+// Single view: rows of n values, columns past d give agg = +0.
 __global__ void __launch_bounds__(256)
-gather_update_generic_kernel(const float* __restrict__ h, float* __restrict__ g,
-                             const int32_t* __restrict__ idx,
-                             float* __restrict__ agg, float* __restrict__ G, int64_t K_total,
-                             int64_t d, int64_t n, int64_t m, int32_t N) {
+gather_update_rows_kernel(const float* __restrict__ h, float* __restrict__ g,
+                          const int32_t* __restrict__ idx, float* __restrict__ agg,
+                          float* __restrict__ G, int64_t K_total, int64_t d, int64_t n,
+                          int64_t m, int32_t N) {
+  const int64_t per_row = (n + 3) / 4;
   const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (tid >= K_total * n) return;
-  const int64_t q = tid / n;
-  const int64_t j = tid - q * n;
+  if (tid >= K_total * per_row) return;
+  const int64_t q = tid / per_row;
+  const int64_t col = (tid - q * per_row) * 4;
   const int64_t p = idx[q];
-  const int64_t e = p * n + j;
-  float acc = 0.0f;
-  if (p >= 0 && p < m && e < d) {
-    for (int32_t i = 0; i < N; ++i) {
-      const int64_t at = (int64_t)i * d + e;
-      const float dl = h[at] - g[at];
-      acc = (i == 0) ? dl : acc + dl;
-      g[at] = g[at] + dl;
-    }
-    if (G) G[e] = G[e] + acc;
-  }
-  agg[tid] = acc;
+  const int width = (int)(n - col < 4 ? n - col : 4);
+  const int64_t e = p * n + col;
+  int live = 0;  // columns that exist (none where idx holds no row: the state stays alone)
+  if (p >= 0 && p < m && e < d) live = (int)(d - e < width ? d - e : width);
+  const float4 acc = move_columns(h, g, G, e, live, d, N);
+  store_columns(agg + q * n + col, acc, width);
 }
 
 // ---------------------------------------------------------------------------
-// Per-tensor mode: one work item = one selected row x 4 columns of a tensor.
-// Items are numbered tensor after tensor (GatherBucket::work_off); a thread
-// finds its tensor by binary search.  Same arithmetic as above: for each
-// worker in ascending order Delta = h - g, agg += Delta, g = g + Delta.
+// Per-tensor mode: items are numbered tensor after tensor
+// (GatherBucket::work_off); a thread finds its tensor by binary search, over
+// an LDS copy of the offsets where they fit, so that the search is one read
+// of global memory deep.
 // ---------------------------------------------------------------------------
+constexpr int kSearchBuckets = 1024;
+
 __global__ void __launch_bounds__(256)
 gather_update_tensors_kernel(const float* __restrict__ h, float* __restrict__ g,
                              const int32_t* __restrict__ idx,
                              float* __restrict__ agg, float* __restrict__ G,
                              const GatherBucket* __restrict__ buckets,
                              int32_t nb, int64_t total_work, int64_t d,
-                             int32_t N, int32_t allow_vec) {
+                             int32_t N) {
+  __shared__ int64_t first[kSearchBuckets];
   const int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const bool in_lds = nb <= kSearchBuckets;
+  if (in_lds) {
+    for (int32_t b = threadIdx.x; b < nb; b += blockDim.x) first[b] = buckets[b].work_off;
+    __syncthreads();
+  }
   if (w >= total_work) return;
   int32_t lo = 0, hi = nb;  // last bucket whose work_off <= w
   while (hi - lo > 1) {
     const int32_t mid = (lo + hi) >> 1;
-    if (buckets[mid].work_off <= w) lo = mid; else hi = mid;
+    if ((in_lds ? first[mid] : buckets[mid].work_off) <= w) lo = mid; else hi = mid;
   }
   const GatherBucket bk = buckets[lo];
   const int64_t per_row = (bk.cols + 3) / 4;
@@ -148,78 +150,24 @@ gather_update_tensors_kernel(const float* __restrict__ h, float* __restrict__ g,
   const int64_t q = item / per_row;
   const int64_t col = (item - q * per_row) * 4;
   const int64_t p = (int64_t)idx[bk.out_off + q] - bk.row0;
-  float* out = agg + bk.agg_off + q * bk.cols + col;
-  const int64_t ncols = bk.cols - col < 4 ? bk.cols - col : 4;
+  const int ncols = (int)(bk.cols - col < 4 ? bk.cols - col : 4);
   const int64_t e = bk.elem_off + p * bk.cols + col;
   // Only rows of this tensor; the bounds keep a broken index from touching
   // memory outside the vectors.
   if (p < 0 || p >= bk.rows || q >= bk.k || e + ncols > d) return;
-  if (bk.vec && allow_vec) {
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int32_t i = 0; i < N; ++i) {
-      const int64_t at = (int64_t)i * d + e;
-      const float4 hv = *reinterpret_cast<const float4*>(h + at);
-      const float4 gv = *reinterpret_cast<const float4*>(g + at);
-      float4 dl;
-      dl.x = hv.x - gv.x;
-      dl.y = hv.y - gv.y;
-      dl.z = hv.z - gv.z;
-      dl.w = hv.w - gv.w;
-      if (i == 0) {
-        acc = dl;
-      } else {
-        acc.x = acc.x + dl.x;
-        acc.y = acc.y + dl.y;
-        acc.z = acc.z + dl.z;
-        acc.w = acc.w + dl.w;
-      }
-      float4 gn;
-      gn.x = gv.x + dl.x;
-      gn.y = gv.y + dl.y;
-      gn.z = gv.z + dl.z;
-      gn.w = gv.w + dl.w;
-      *reinterpret_cast<float4*>(g + at) = gn;
-    }
-    if (G) {
-      float4 Gv = *reinterpret_cast<const float4*>(G + e);
-      Gv.x = Gv.x + acc.x;
-      Gv.y = Gv.y + acc.y;
-      Gv.z = Gv.z + acc.z;
-      Gv.w = Gv.w + acc.w;
-      *reinterpret_cast<float4*>(G + e) = Gv;
-    }
-    *reinterpret_cast<float4*>(out) = acc;
-  } else {
-    for (int64_t jj = 0; jj < ncols; ++jj) {
-      float acc = 0.0f;
-      for (int32_t i = 0; i < N; ++i) {
-        const int64_t at = (int64_t)i * d + e + jj;
-        const float dl = h[at] - g[at];
-        acc = (i == 0) ? dl : acc + dl;
-        g[at] = g[at] + dl;
-      }
-      if (G) G[e + jj] = G[e + jj] + acc;
-      out[jj] = acc;
-    }
-  }
+  const float4 acc = move_columns(h, g, G, e, ncols, d, N);
+  store_columns(agg + bk.agg_off + q * bk.cols + col, acc, ncols);
 }
 
 }  // namespace
 
-hipError_t launch_gather_update(bool fast, const float* h, float* g,
+hipError_t launch_gather_update(const float* h, float* g,
                                 const int32_t* idx, float* agg, float* G, int64_t K_total,
                                 int64_t d, int64_t n, int64_t m, int32_t N,
                                 hipStream_t stream) {
   if (K_total <= 0) return hipSuccess;
-  if (fast) {
-    hipLaunchKernelGGL(gather_update_fast_kernel,
-                       dim3(blocks_for(K_total * (n / 4), 256)), dim3(256), 0,
-                       stream, h, g, idx, agg, G, K_total, d, n, m, N);
-  } else {
-    hipLaunchKernelGGL(gather_update_generic_kernel,
-                       dim3(blocks_for(K_total * n, 256)), dim3(256), 0, stream,
-                       h, g, idx, agg, G, K_total, d, n, m, N);
-  }
+  hipLaunchKernelGGL(gather_update_rows_kernel, dim3(blocks_for(K_total * ((n + 3) / 4), 256)),
+                     dim3(256), 0, stream, h, g, idx, agg, G, K_total, d, n, m, N);
   return hipGetLastError();
 }
 
@@ -227,11 +175,10 @@ hipError_t launch_gather_update_tensors(const float* h, float* g,
                                         const int32_t* idx, float* agg, float* G,
                                         const GatherBucket* buckets, int32_t nb,
                                         int64_t total_work, int64_t d, int32_t N,
-                                        bool allow_vec, hipStream_t stream) {
+                                        hipStream_t stream) {
   if (total_work <= 0) return hipSuccess;
   hipLaunchKernelGGL(gather_update_tensors_kernel, dim3(blocks_for(total_work, 256)),
-                     dim3(256), 0, stream, h, g, idx, agg, G, buckets, nb, total_work, d, N,
-                     allow_vec ? 1 : 0);
+                     dim3(256), 0, stream, h, g, idx, agg, G, buckets, nb, total_work, d, N);
   return hipGetLastError();
 }
 
