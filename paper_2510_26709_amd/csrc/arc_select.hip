@@ -166,15 +166,22 @@ radix_pass_kernel(const float* __restrict__ sigma, SelectWorkspace ws) {
   uint32_t keys[kTileKeys];
   load_tile(sigma, bd.lo, bd.hi, keys);
   const BucketState st = state_before_pass<PASS>(ws, bk, bd.bucket);  // syncs
+  uint32_t zeros = 0;
   for (int64_t tile = bd.lo; tile < bd.hi; tile += kTileRows) {
 #pragma unroll
     for (int u = 0; u < kTileKeys; ++u) {
       const int64_t p = tile + (int64_t)u * kSelectThreads + threadIdx.x;
-      if (p < bd.hi && (keys[u] & st.mask) == st.prefix)
-        atomicAdd(&lhist[(keys[u] >> D::kShift) & D::kMask], 1u);
+      const bool in = p < bd.hi && (keys[u] & st.mask) == st.prefix;
+      // Rows whose residual is zero (tokens a batch did not hold, say) share
+      // the one key 0: counted apart, as one LDS address would take their
+      // adds in turn.
+      zeros += in && keys[u] == 0u;
+      if (in && keys[u] != 0u) atomicAdd(&lhist[(keys[u] >> D::kShift) & D::kMask], 1u);
     }
     if (tile + kTileRows < bd.hi) load_tile(sigma, tile + kTileRows, bd.hi, keys);
   }
+  zeros = wave_sum(zeros);
+  if ((threadIdx.x & (kWave - 1)) == 0 && zeros != 0u) atomicAdd(&lhist[0], zeros);
   __syncthreads();
   uint32_t* gh = hist_of_mut(ws, PASS, bd.bucket);
   for (int b = threadIdx.x; b < D::kBins; b += kSelectThreads) {
