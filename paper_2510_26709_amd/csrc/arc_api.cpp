@@ -217,9 +217,9 @@ struct GroupLists {
 // List of vectorisable groups of that many rows: 16-byte aligned rows, or any.
 int size_slot(int32_t group_rows, bool aligned) {
   return (group_rows == 64 ? 0 : group_rows == 32 ? 1 : group_rows == 16 ? 2 : 3) +
-         (aligned ? 0 : arc::kVecLists / 2);
+         (aligned ? 0 : arc::kWindowLists / 2);
 }
-int32_t slot_rows(int slot) { return 64 >> slot % (arc::kVecLists / 2); }
+int32_t slot_rows(int slot) { return 64 >> slot % (arc::kWindowLists / 2); }
 
 // Occupancy of one vectorised sketch launch from its groups' mean number of
 // chunks per row (weighted by coordinates).  A wave streams one chunk while
@@ -279,15 +279,61 @@ int32_t row_interleave(int64_t cols, int32_t group_rows) {
   return span <= (int64_t{1} << 30) ? static_cast<int32_t>(S) : 1;
 }
 
+// The kernels a view's rows can take: those of arc_sketch_general.hip,
+// arc_sketch.hip (column windows), arc_span.hip and arc_lines.hip.
+enum class RowKernel { kGeneral, kWindow, kSpan, kLines };
+
+// Rows off the 128-byte lines (a width or a worker base that is not a multiple
+// of 32 values): spans where at least five rows fit in one, else the lines
+// kernel.  Step us on 2.0e7 values, 4 workers, span / window kernels on the
+// rows as they lie: 800 values 269 / 531, 801 311 / 324, 1001 378 / 312 (four
+// rows a span); the lines kernel takes 281 at 1001.  A span row shorter than
+// four values can end twice within one 16-byte access, so only a lone row may
+// be.
+constexpr int64_t kSpanMaxCols = arc::kSpanValues / 5;
+constexpr int64_t kSpanMinCols = 4;
+RowKernel off_line_kernel(int64_t rows, int64_t cols) {
+  if (cols <= kSpanMaxCols)
+    return cols >= kSpanMinCols || rows == 1 ? RowKernel::kSpan : RowKernel::kWindow;
+  return RowKernel::kLines;
+}
+
+// Groups of the span kernel: as many consecutive rows as fit, up to 64.
+void add_span_groups(int64_t elem_off, int64_t row0, int64_t rows, int64_t cols, int64_t v_off,
+                     GroupLists* out) {
+  const int64_t step =
+      std::min<int64_t>(kGroupRows, std::max<int64_t>(1, arc::kSpanValues / cols));
+  for (int64_t p = 0; p < rows; p += step) {
+    arc::RowGroup grp{};
+    grp.elem_off = elem_off + p * cols;
+    grp.row0 = row0 + p;
+    grp.v_off = v_off;
+    grp.rows = static_cast<int32_t>(std::min(step, rows - p));
+    grp.cols = static_cast<int32_t>(cols);
+    grp.last_len = grp.cols;
+    grp.stride = 1;
+    out->vec[arc::kSpanList].push_back(grp);
+  }
+}
+
 // Row groups over `rows` rows of width `cols` that start at coordinate
-// elem_off and global row row0; the last row holds last_len <= cols values.
-// group_rows > 0: vectorisable groups of that many rows (the view has no
-// ragged row), `aligned` where every worker's rows start on 16 bytes and end
-// there (given 16-byte aligned arrays); 0: general groups of 64 rows.
-// Vectorised groups take every S-th row of a block of S*G consecutive rows
-// (S groups per block), the rest consecutive rows.
+// elem_off and global row row0; the last row holds last_len <= cols values
+// (fewer than cols in general groups only).  kWindow: `aligned` where every
+// worker's rows start on 16 bytes and end there (given 16-byte aligned
+// arrays).
+// The groups of the window and lines kernels take every S-th row of a block
+// of S*G consecutive rows (S groups per block), the rest consecutive rows.
 void add_groups(int64_t elem_off, int64_t row0, int64_t rows, int64_t cols, int64_t last_len,
-                int64_t v_off, int32_t group_rows, bool aligned, GroupLists* out) {
+                int64_t v_off, RowKernel kernel, bool aligned, GroupLists* out) {
+  if (kernel == RowKernel::kSpan)
+    return add_span_groups(elem_off, row0, rows, cols, v_off, out);
+  const int32_t group_rows = kernel == RowKernel::kWindow  ? vector_group_rows(cols)
+                             : kernel == RowKernel::kLines ? arc::kLineRows
+                                                           : 0;
+  std::vector<arc::RowGroup>& list =
+      kernel == RowKernel::kWindow  ? out->vec[size_slot(group_rows, aligned)]
+      : kernel == RowKernel::kLines ? out->vec[arc::kLinesList]
+                                    : out->general;
   const int64_t step = group_rows > 0 ? group_rows : kGroupRows;
   auto push = [&](int64_t p, int64_t nrows, int32_t stride) {
     arc::RowGroup grp{};
@@ -298,7 +344,7 @@ void add_groups(int64_t elem_off, int64_t row0, int64_t rows, int64_t cols, int6
     grp.cols = static_cast<int32_t>(cols);
     grp.last_len = static_cast<int32_t>(p + (nrows - 1) * stride == rows - 1 ? last_len : cols);
     grp.stride = stride;
-    (group_rows > 0 ? out->vec[size_slot(group_rows, aligned)] : out->general).push_back(grp);
+    list.push_back(grp);
   };
   int64_t p = 0;
   const int32_t S = group_rows > 0 ? row_interleave(cols, group_rows) : 1;
@@ -340,18 +386,23 @@ void build_plan(const arc_config* cfg, arc_ctx* c) {
     // any) holds the d - m_full*n remaining coordinates.
     c->widths.push_back(c->n);
     c->v_off[c->n] = 0;
-    c->v_floats = c->n * c->r;
+    c->v_floats = (c->n * c->r + 3) / 4 * 4;  // read as whole float4s
     const int64_t m_full = c->d / c->n;
-    const int32_t gr = r_ok ? vector_group_rows(c->n) : 0;
-    if (gr > 0) {
+    if (r_ok && vector_group_rows(c->n) > 0) {
+      // The ragged row is a one-row group as wide as its values, in the same
+      // launch as the others.
       const bool aligned = c->d % 4 == 0 && c->n % 4 == 0;
-      add_groups(0, 0, m_full, c->n, c->n, 0, gr, aligned, &lists);
-      // The ragged row is a one-row group as wide as its values (a multiple
-      // of 4 of them where d and n are).
+      // Rows on 16 bytes that all start the same distance past a line keep
+      // the window kernels' common shift where they are wide.
+      const bool on_lines = c->n % 32 == 0 && (c->d % 32 == 0 || (aligned && c->n > kSpanMaxCols));
+      const RowKernel kernel = on_lines ? RowKernel::kWindow : off_line_kernel(m_full, c->n);
       const int64_t tail = c->d - m_full * c->n;
-      if (tail > 0) add_groups(m_full * c->n, m_full, 1, tail, tail, 0, gr, aligned, &lists);
+      add_groups(0, 0, m_full, c->n, c->n, 0, kernel, aligned, &lists);
+      if (tail > 0)
+        add_groups(m_full * c->n, m_full, 1, tail, tail, 0, kernel, aligned, &lists);
     } else {
-      add_groups(0, 0, c->m, c->n, c->d - (c->m - 1) * c->n, 0, 0, false, &lists);
+      add_groups(0, 0, c->m, c->n, c->d - (c->m - 1) * c->n, 0, RowKernel::kGeneral, false,
+                 &lists);
     }
     if (cfg->num_buckets == 0) {
       begin.push_back(c->m);
@@ -393,9 +444,14 @@ void build_plan(const arc_config* cfg, arc_ctx* c) {
     int64_t off = 0, row0 = 0;
     for (int32_t b = 0; b < cfg->num_tensors; ++b) {
       const arc_tensor& t = cfg->tensors[b];
-      const int32_t gr = r_ok ? vector_group_rows(t.cols) : 0;
       const bool aligned = c->d % 4 == 0 && off % 4 == 0 && t.cols % 4 == 0;
-      add_groups(off, row0, t.rows, t.cols, t.cols, c->v_off[t.cols], gr, aligned, &lists);
+      // Tensors on 16 bytes keep the window kernels, whose launches they
+      // share (per-tensor ResNet-18 377 us, 382 with its rows off the lines
+      // in the span and lines kernels).
+      const RowKernel kernel = !r_ok || vector_group_rows(t.cols) == 0 ? RowKernel::kGeneral
+                               : aligned ? RowKernel::kWindow
+                                         : off_line_kernel(t.rows, t.cols);
+      add_groups(off, row0, t.rows, t.cols, t.cols, c->v_off[t.cols], kernel, aligned, &lists);
       off += t.rows * t.cols;
       row0 += t.rows;
       begin.push_back(row0);
@@ -429,12 +485,16 @@ void build_plan(const arc_config* cfg, arc_ctx* c) {
   c->groups.clear();
   for (int sz = 0; sz < arc::kVecLists; ++sz) {
     c->vec_count[sz] = static_cast<int64_t>(lists.vec[sz].size());
-    c->vec_occ[sz] = sketch_occupancy(lists.vec[sz], slot_rows(sz));
+    if (sz < arc::kWindowLists) c->vec_occ[sz] = sketch_occupancy(lists.vec[sz], slot_rows(sz));
     for (const arc::RowGroup& grp : lists.vec[sz])
       c->stage_elems[sz] += (grp.rows - 1) * static_cast<int64_t>(grp.cols) + grp.last_len;
     c->groups.insert(c->groups.end(), lists.vec[sz].begin(), lists.vec[sz].end());
   }
   c->nvec_groups = static_cast<int64_t>(c->groups.size());
+  for (const arc::RowGroup& grp : lists.vec[arc::kSpanList])
+    c->span_floats = std::max(
+        c->span_floats, arc::span_wave_floats(grp.rows, grp.cols,
+                                              c->compressor == ARC_COMP_ARC ? c->r : 0));
   c->groups.insert(c->groups.end(), lists.general.begin(), lists.general.end());
   for (const arc::RowGroup& grp : lists.general)
     c->stage_elems[arc::kVecLists] += (grp.rows - 1) * static_cast<int64_t>(grp.cols) + grp.last_len;
@@ -739,9 +799,23 @@ arc_status launch_streaming_stage(arc_ctx* c, const void* grad, float* h, const 
       }
       int64_t first = 0;
       for (int sz = 0; sz < w; ++sz) first += c->vec_count[sz];
-      const int32_t gr = slot_rows(w);
-      const bool unaligned = !aligned || w >= kLists / 2;
       const arc::RowGroup* grp = c->groups_dev + first;
+      if (w == arc::kSpanList) {
+        ARC_HIP(arc::launch_sketch_span(grad, c->grad_bf16, h, g, c->V_dev, grp, c->vec_count[w],
+                                        c->S_dev, c->d, c->m, c->N, norm ? 1 : c->r, c->eta,
+                                        c->a, norm, c->span_floats, s),
+                "sketch launch (narrow rows)");
+        continue;
+      }
+      if (w == arc::kLinesList) {
+        ARC_HIP(arc::launch_sketch_lines(grad, c->grad_bf16, h, g, c->V_dev, grp,
+                                         c->vec_count[w], c->S_dev, c->d, c->m, c->N,
+                                         norm ? 1 : c->r, c->eta, c->a, norm, s),
+                "sketch launch (rows off the lines)");
+        continue;
+      }
+      const int32_t gr = slot_rows(w);
+      const bool unaligned = !aligned || w >= arc::kWindowLists / 2;
       if (norm) {
         ARC_HIP(arc::launch_row_norms(gr, unaligned, grad, c->grad_bf16, h, g, c->V_dev, grp,
                                       c->vec_count[w], c->S_dev, c->d, c->m, c->N, c->eta, c->a,
@@ -984,7 +1058,8 @@ arc_status arc_describe(const arc_ctx* c, char* buf, int64_t len) {
   std::snprintf(buf, static_cast<size_t>(len),
                 "compressor=%s mode=%s sketch=%s widths=%zu row_groups=%lld vector_groups=%lld "
                 "(64:%lld 32:%lld 16:%lld 8:%lld rows) workgroup_waves=(%d%s %d%s %d%s %d%s) "
-                "interleaved_groups=%lld unaligned_groups=%lld general_groups=%lld "
+                "interleaved_groups=%lld unaligned_groups=%lld span_groups=%lld "
+                "line_groups=%lld general_groups=%lld "
                 "lds_limit=%zu buckets=%zu radix_buckets=%d select=%s%s K_total=%lld "
                 "payload=%lld",
                 comp, c->tensor_mode ? "tensors" : "single_view", sketch, c->widths.size(),
@@ -993,6 +1068,8 @@ arc_status arc_describe(const arc_ctx* c, char* buf, int64_t len) {
                 occ[0].one_per_cu ? "/cu" : "", occ[1].waves, occ[1].one_per_cu ? "/cu" : "",
                 occ[2].waves, occ[2].one_per_cu ? "/cu" : "", occ[3].waves,
                 occ[3].one_per_cu ? "/cu" : "", strided, unaligned,
+                static_cast<long long>(c->vec_count[arc::kSpanList]),
+                static_cast<long long>(c->vec_count[arc::kLinesList]),
                 static_cast<long long>(ngroups - c->nvec_groups),
                 c->max_lds_per_block, c->buckets.size(),
                 radix, c->select_ws().small ? "one_workgroup_per_bucket" : "blocks:",

@@ -18,8 +18,13 @@
 
 namespace arc {
 
-// Lists of vectorisable row groups: four group sizes, aligned and unaligned.
-constexpr int kVecLists = 8;
+// Lists of vectorisable row groups: four group sizes, aligned and unaligned,
+// for the column-window kernels, then the groups of narrow rows and of wide
+// rows off the lines.
+constexpr int kWindowLists = 8;
+constexpr int kSpanList = kWindowLists;
+constexpr int kLinesList = kWindowLists + 1;
+constexpr int kVecLists = kWindowLists + 2;
 
 // HIP events recorded per step when stage timing is on.
 constexpr int kEventsPerStep = 6;
@@ -62,12 +67,14 @@ struct arc_ctx {
   int64_t v_floats = 0;
   // row groups, one list per launch: the vectorisable ones with 16-byte
   // aligned rows by group size (64, 32, 16, 8 rows: lists 0-3), those with
-  // any other rows by group size (lists 4-7), then the general ones
+  // any other rows by group size (lists 4-7), narrow rows (list 8),
+  // wide rows off the lines (list 9), then the general ones
   std::vector<arc::RowGroup> groups;
   int64_t nvec_groups = 0;
   std::array<int64_t, arc::kVecLists> vec_count{};  // groups per vectorisable list
   std::array<int64_t, arc::kVecLists + 1> stage_elems{};  // coordinates per list, general last
-  std::array<arc::SketchOccupancy, arc::kVecLists> vec_occ{};  // launch shape per list
+  std::array<arc::SketchOccupancy, arc::kWindowLists> vec_occ{};  // launch shapes
+  int32_t span_floats = 0;  // LDS floats of a wave of the narrow rows' launch
   // per-tensor gather
   std::vector<arc::GatherBucket> gather;
   int64_t gather_work = 0;

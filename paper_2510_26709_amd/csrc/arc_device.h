@@ -99,6 +99,19 @@ __device__ __forceinline__ void buffer_store_f4(buffer_rsrc r, uint32_t off, flo
   __builtin_amdgcn_raw_buffer_store_b128(w, r, (int)off, 0, kPolicy);
 }
 
+// 16 bytes a lane from off (zeros past the resource's end) to the wave's LDS
+// at dst + 4 * lane floats, without a register in between.  Counts as a
+// vector memory load: wave_vmem_fence() waits for it.
+__device__ __forceinline__ void buffer_load_lds_f4(buffer_rsrc r, uint32_t off, float* dst) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(
+      r, (__attribute__((address_space(3))) void*)dst, 16, (int)off, 0, 0, 0);
+}
+
+// All of this wave's vector memory accesses issued before have completed.
+__device__ __forceinline__ void wave_vmem_fence() {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
 // Workgroups are dispatched round-robin over the 8 XCDs of the MI355X (block
 // b starts on XCD b % 8).  This bijection of [0, nblocks) hands each XCD one
 // contiguous range of blocks (the last nblocks % 8 map to themselves).

@@ -130,6 +130,34 @@ hipError_t launch_sketch_per_worker(int32_t group_rows, bool unaligned, const vo
                                     int64_t d, int64_t m, int32_t N, int32_t r, float eta,
                                     float a, SketchOccupancy occ, hipStream_t stream);
 
+// Narrow rows (arc_span.hip): the same results for groups of up to 64
+// consecutive rows of at most kSpanValues values in all, any alignment, r in
+// {1, 2, 4, 8}.  norm (r = 1): squared row norms instead of sketches.
+// wave_floats: the largest span_wave_floats of the groups.
+constexpr int32_t kSpanValues = 4096;
+// LDS floats from one row to the next: whole float4s, an odd number of them,
+// so that lanes reading the same columns of consecutive rows hit distinct
+// banks.
+__host__ __device__ constexpr int32_t span_pitch(int32_t n) { return (((n + 3) / 4) | 1) * 4; }
+// LDS floats of a wave: its rows of Delta, and V of the rows' width (in whole
+// loads of 64 lanes), and four to spare.
+constexpr int32_t span_wave_floats(int32_t rows, int32_t n, int32_t r) {
+  return rows * span_pitch(n) + (n * r + 255) / 256 * 256 + 4;
+}
+hipError_t launch_sketch_span(const void* grad, int32_t grad_bf16, float* h, const float* g,
+                              const float* V, const RowGroup* groups, int64_t ngroups, float* S,
+                              int64_t d, int64_t m, int32_t N, int32_t r, float eta, float a,
+                              bool norm, int32_t wave_floats, hipStream_t stream);
+
+// Wide rows off the 128-byte lines (arc_lines.hip): the same results for
+// groups of at most kLineRows rows of any width up to 2^22, any alignment, r
+// in {1, 2, 4, 8}.  norm (r = 1): squared row norms instead of sketches.
+constexpr int32_t kLineRows = 8;
+hipError_t launch_sketch_lines(const void* grad, int32_t grad_bf16, float* h, const float* g,
+                               const float* V, const RowGroup* groups, int64_t ngroups, float* S,
+                               int64_t d, int64_t m, int32_t N, int32_t r, float eta, float a,
+                               bool norm, hipStream_t stream);
+
 // The same for any row group (any width, r <= ARC_MAX_R, element alignment,
 // ragged last row), one wave per (group, worker).  norm (r = 1): S holds each
 // row's squared norm of Delta instead of its sketch.

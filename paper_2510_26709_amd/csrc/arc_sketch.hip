@@ -86,11 +86,13 @@ constexpr uint32_t kDropOffset = 0x80000000u;
 // that starts in the upper half of a word is read as the two or three words
 // that hold each quad and shifted into place; the last n % 4 columns of every
 // row are taken one value per lane, loaded before the first chunk and chained
-// after the last.  Bound by HBM like the aligned kernel, less the lines that
-// two accesses share.  Such rows used to take one value per lane throughout:
-// step times before / after, 4 workers, per-tensor CIFAR ResNet-18 (11.2e6
-// binary32 values a worker, 2 past a multiple of 4) 1.266 / 0.309 ms; 3.0e6
-// bf16 values of 640 a row 0.199 / 0.097 ms.
+// after the last.  Taken by layouts planned for 16-byte rows whose arrays are
+// off 16 bytes, and by rows of one to three values; other rows off the lines
+// have kernels of their own (arc_span.hip, arc_lines.hip).  Bound by HBM like
+// the aligned kernel, less the lines that two accesses share: 2.0e7 binary32
+// values of 3001 a row, 4 workers, 0.316 ms a step, where one value per lane
+// throughout, as such rows once took, is 4-5 times slower (per-tensor CIFAR
+// ResNet-18 1.266 ms, 0.309 through this kernel).
 // NORM (R = 1): the chain is the row's squared
 // norm, fmaf(Delta, Delta, s), and V is unused.
 template <int R, bool BF16, int G, bool NORM, bool UNAL>

@@ -18,11 +18,12 @@ def _gpu():
         pytest.skip("no GPU")
 
 
-# Widths around the group sizes' chunks (32, 64, 128, 256 columns) and the
-# quads: rows of one to three values, of 1 to 3 values past a chunk or short
-# of one, of several chunks, and whole quads on an odd worker base.
-WIDTHS = [1, 2, 3, 5, 31, 33, 62, 65, 127, 129, 147, 255, 257, 259, 510, 513, 576, 1001, 1026,
-          2303, 4099]
+# Rows of one to three values (window kernels), of four to 819 (spans: up to
+# 64 rows, down to five) and of more (lines kernel): around whole quads,
+# around the 256-column chunks less the line's lag, and whole quads on an odd
+# worker base.
+WIDTHS = [1, 2, 3, 4, 5, 6, 31, 33, 62, 65, 127, 129, 147, 255, 257, 259, 510, 513, 576, 818, 819,
+          820, 821, 990, 992, 993, 1001, 1024, 1026, 2303, 4099]
 
 
 @pytest.mark.parametrize("n", WIDTHS)
@@ -35,6 +36,16 @@ def test_parity_odd_widths(n, dtype):
         log(f"[unaligned] n={n} {dtype} r={r} N={N} d={d} misalign={mis}")
         run_case(label=f"odd_{n}_{dtype}_{k}", d=d, N=N, n=n, r=r, K=rows // 7 + 1, steps=2,
                  grad_dtype=dtype, family=1 if dtype == "bf16" else 0, misalign=mis, check_S=True)
+
+
+# Wide rows in groups of every 4th row (2307, 5001 values) and of every 4th
+# and 2nd at power-of-two widths, with a ragged tail row.
+@pytest.mark.parametrize("n,dtype,mis", [(2307, "f32", 1), (2307, "bf16", 0), (5001, "bf16", 3),
+                                         (2048, "f32", 0), (4096, "bf16", 1)])
+def test_parity_strided_rows_off_lines(n, dtype, mis):
+    log(f"[unaligned] strided n={n} {dtype} misalign={mis}")
+    run_case(label=f"strided_{n}_{dtype}", d=n * 70 + 1001, N=3, n=n, r=4, K=9, steps=2,
+             grad_dtype=dtype, family=1 if dtype == "bf16" else 0, misalign=mis, check_S=True)
 
 
 # Tensors on either side of a 16-byte boundary in one layout: aligned lists,
