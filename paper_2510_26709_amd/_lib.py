@@ -237,7 +237,7 @@ def arc_last_error() -> str:
 
 
 def arc_describe(ctx) -> str:
-    buf = ctypes.create_string_buffer(512)
+    buf = ctypes.create_string_buffer(1024)
     _check(_lib.arc_describe(ctx, buf, len(buf)), "arc_describe")
     return buf.value.decode()
 

@@ -318,16 +318,17 @@ void add_span_groups(int64_t elem_off, int64_t row0, int64_t rows, int64_t cols,
 
 // Row groups over `rows` rows of width `cols` that start at coordinate
 // elem_off and global row row0; the last row holds last_len <= cols values
-// (fewer than cols in general groups only).  kWindow: `aligned` where every
-// worker's rows start on 16 bytes and end there (given 16-byte aligned
-// arrays).
+// (fewer than cols in general groups only).  kWindow: groups of window_rows
+// rows, `aligned` where every worker's rows start on 16 bytes and end there
+// (given 16-byte aligned arrays).
 // The groups of the window and lines kernels take every S-th row of a block
 // of S*G consecutive rows (S groups per block), the rest consecutive rows.
 void add_groups(int64_t elem_off, int64_t row0, int64_t rows, int64_t cols, int64_t last_len,
-                int64_t v_off, RowKernel kernel, bool aligned, GroupLists* out) {
+                int64_t v_off, RowKernel kernel, int32_t window_rows, bool aligned,
+                GroupLists* out) {
   if (kernel == RowKernel::kSpan)
     return add_span_groups(elem_off, row0, rows, cols, v_off, out);
-  const int32_t group_rows = kernel == RowKernel::kWindow  ? vector_group_rows(cols)
+  const int32_t group_rows = kernel == RowKernel::kWindow  ? window_rows
                              : kernel == RowKernel::kLines ? arc::kLineRows
                                                            : 0;
   std::vector<arc::RowGroup>& list =
@@ -388,7 +389,8 @@ void build_plan(const arc_config* cfg, arc_ctx* c) {
     c->v_off[c->n] = 0;
     c->v_floats = (c->n * c->r + 3) / 4 * 4;  // read as whole float4s
     const int64_t m_full = c->d / c->n;
-    if (r_ok && vector_group_rows(c->n) > 0) {
+    const int32_t gr = r_ok ? vector_group_rows(c->n) : 0;
+    if (gr > 0) {
       // The ragged row is a one-row group as wide as its values, in the same
       // launch as the others.
       const bool aligned = c->d % 4 == 0 && c->n % 4 == 0;
@@ -397,11 +399,11 @@ void build_plan(const arc_config* cfg, arc_ctx* c) {
       const bool on_lines = c->n % 32 == 0 && (c->d % 32 == 0 || (aligned && c->n > kSpanMaxCols));
       const RowKernel kernel = on_lines ? RowKernel::kWindow : off_line_kernel(m_full, c->n);
       const int64_t tail = c->d - m_full * c->n;
-      add_groups(0, 0, m_full, c->n, c->n, 0, kernel, aligned, &lists);
+      add_groups(0, 0, m_full, c->n, c->n, 0, kernel, gr, aligned, &lists);
       if (tail > 0)
-        add_groups(m_full * c->n, m_full, 1, tail, tail, 0, kernel, aligned, &lists);
+        add_groups(m_full * c->n, m_full, 1, tail, tail, 0, kernel, gr, aligned, &lists);
     } else {
-      add_groups(0, 0, c->m, c->n, c->d - (c->m - 1) * c->n, 0, RowKernel::kGeneral, false,
+      add_groups(0, 0, c->m, c->n, c->d - (c->m - 1) * c->n, 0, RowKernel::kGeneral, 0, false,
                  &lists);
     }
     if (cfg->num_buckets == 0) {
@@ -448,10 +450,12 @@ void build_plan(const arc_config* cfg, arc_ctx* c) {
       // Tensors on 16 bytes keep the window kernels, whose launches they
       // share (per-tensor ResNet-18 377 us, 382 with its rows off the lines
       // in the span and lines kernels).
-      const RowKernel kernel = !r_ok || vector_group_rows(t.cols) == 0 ? RowKernel::kGeneral
+      const int32_t gr = r_ok ? vector_group_rows(t.cols) : 0;
+      const RowKernel kernel = gr == 0   ? RowKernel::kGeneral
                                : aligned ? RowKernel::kWindow
                                          : off_line_kernel(t.rows, t.cols);
-      add_groups(off, row0, t.rows, t.cols, t.cols, c->v_off[t.cols], kernel, aligned, &lists);
+      add_groups(off, row0, t.rows, t.cols, t.cols, c->v_off[t.cols], kernel, gr, aligned,
+                 &lists);
       off += t.rows * t.cols;
       row0 += t.rows;
       begin.push_back(row0);

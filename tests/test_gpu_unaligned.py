@@ -71,3 +71,23 @@ def test_topk_norms_unaligned(n, dtype, mis):
     log(f"[unaligned] topk n={n} {dtype} misalign={mis}")
     run_compare_case(compressor="topk", d=n * 70 + n // 2, N=3, n=n, K=6, grad_dtype=dtype,
                      family=1 if dtype == "bf16" else 0, misalign=mis, label=f"topk_{n}_{dtype}")
+
+
+def test_ragged_row_shares_the_launch_of_its_view():
+    # Rows on the lines and off them, narrow and wide, on 16 bytes and not:
+    # the tail row never adds a list of its own (each non-empty list is one
+    # launch of the streaming stage).
+    import re
+
+    import paper_2510_26709_amd as arc
+    for n, d in ((3904, 3904 * 50 + 36), (2048, 2048 * 50 + 32), (512, 512 * 90 + 40),
+                 (333, 333 * 90 + 2), (1001, 1001 * 50 + 3), (4099, 4099 * 40 + 1)):
+        comp = arc.Compressor(d=d, N=2, n=n, r=4, K=3, eta=0.1, seed=1)
+        try:
+            desc = comp.describe()
+        finally:
+            comp.close()
+        windows = re.search(r"\(64:(\d+) 32:(\d+) 16:(\d+) 8:(\d+) rows\)", desc).groups()
+        others = [re.search(key + r"_groups=(\d+)", desc).group(1)
+                  for key in ("span", "line", "general")]
+        assert sum(int(c) > 0 for c in list(windows) + others) == 1, (n, d, desc)
