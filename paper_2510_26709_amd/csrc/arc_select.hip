@@ -38,6 +38,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "arc_device.h"
 #include "arc_internal.h"
 
@@ -166,27 +168,56 @@ radix_pass_kernel(const float* __restrict__ sigma, SelectWorkspace ws) {
   uint32_t keys[kTileKeys];
   load_tile(sigma, bd.lo, bd.hi, keys);
   const BucketState st = state_before_pass<PASS>(ws, bk, bd.bucket);  // syncs
+  // Rows whose residual is zero (tokens a batch did not hold, say) share the
+  // one key 0, and one LDS address would take their adds in turn.  In pass 0
+  // the lowest bin (zero and denormal keys) gets what the other bins leave of
+  // the block's rows; later passes count zeros apart, in the case that their
+  // prefix lets them in.  (Counted in a register in every pass, they cost 1 us
+  // a pass where no key is 0.)
   uint32_t zeros = 0;
-  for (int64_t tile = bd.lo; tile < bd.hi; tile += kTileRows) {
+  auto add_tile = [&](int64_t tile, auto apart) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < kTileKeys; ++u) {
       const int64_t p = tile + (int64_t)u * kSelectThreads + threadIdx.x;
-      const bool in = p < bd.hi && (keys[u] & st.mask) == st.prefix;
-      // Rows whose residual is zero (tokens a batch did not hold, say) share
-      // the one key 0: counted apart, as one LDS address would take their
-      // adds in turn.
-      zeros += in && keys[u] == 0u;
-      if (in && keys[u] != 0u) atomicAdd(&lhist[(keys[u] >> D::kShift) & D::kMask], 1u);
+      const uint32_t digit = (keys[u] >> D::kShift) & D::kMask;
+      bool in = p < bd.hi && (PASS == 0 ? digit != 0u : (keys[u] & st.mask) == st.prefix);
+      if constexpr (decltype(apart)::value) {
+        zeros += in && keys[u] == 0u;
+        in = in && keys[u] != 0u;
+      }
+      if (in) atomicAdd(&lhist[digit], 1u);
     }
+  };
+  const bool apart = PASS > 0 && st.prefix == 0u;  // whole block
+  for (int64_t tile = bd.lo; tile < bd.hi; tile += kTileRows) {
+    if (apart)
+      add_tile(tile, std::true_type{});
+    else
+      add_tile(tile, std::false_type{});
     if (tile + kTileRows < bd.hi) load_tile(sigma, tile + kTileRows, bd.hi, keys);
   }
-  zeros = wave_sum(zeros);
-  if ((threadIdx.x & (kWave - 1)) == 0 && zeros != 0u) atomicAdd(&lhist[0], zeros);
+  if (apart) {
+    zeros = wave_sum(zeros);
+    if ((threadIdx.x & (kWave - 1)) == 0 && zeros != 0u) atomicAdd(&lhist[0], zeros);
+  }
   __syncthreads();
   uint32_t* gh = hist_of_mut(ws, PASS, bd.bucket);
+  uint32_t counted = 0;
   for (int b = threadIdx.x; b < D::kBins; b += kSelectThreads) {
     const uint32_t c = lhist[b];
+    counted += c;
     if (c != 0u) atomicAdd(&gh[b], c);
+  }
+  if constexpr (PASS == 0) {
+    __shared__ uint32_t part[kSelectThreads / kWave];
+    counted = wave_sum(counted);
+    if ((threadIdx.x & (kWave - 1)) == 0) part[threadIdx.x / kWave] = counted;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      uint32_t low = (uint32_t)(bd.hi - bd.lo);
+      for (int w = 0; w < kSelectThreads / kWave; ++w) low -= part[w];
+      if (low != 0u) atomicAdd(&gh[0], low);
+    }
   }
 }
 
