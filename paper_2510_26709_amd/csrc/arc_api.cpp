@@ -867,7 +867,7 @@ arc_status enqueue_step(arc_ctx* c, int64_t t, const void* grad, float* h, float
   const arc::SelectWorkspace ws = c->select_ws();
   if (c->compressor == ARC_COMP_RANDK) {
     // Stage 0: Eq. (11a) alone (the residual is needed at the kept rows only).
-    const bool vec = (c->N * c->d) % 4 == 0 && aligned16(grad) && aligned16(h);
+    const bool vec = aligned16(grad) && aligned16(h);
     ARC_HIP(arc::launch_momentum(vec, grad, c->grad_bf16, h, c->N * c->d, c->eta, c->a,
                                  c->stream),
             "momentum launch");
@@ -999,17 +999,6 @@ arc_status arc_model_step(arc_ctx* c, const arc_model_config* mc, int64_t t, con
     }
   }
 
-  if (dense) {
-    const bool vec = c->d % 4 == 0 && aligned16(grad) && aligned16(h) && aligned16(g) &&
-                     aligned16(G);
-    ARC_HIP(arc::launch_dense_step(vec, grad, c->grad_bf16, h, g, G, c->d, c->N, c->eta, c->a,
-                                   c->stream),
-            "dense step launch");
-  } else {
-    st = arc::enqueue_step(c, t, grad, h, g, out_idx, out_agg, G);
-    if (st != ARC_OK) return st;
-  }
-
   arc::OptimizerArgs o{};
   o.kind = mc->optimizer;
   o.neg_lr = -mc->lr;
@@ -1031,6 +1020,20 @@ arc_status arc_model_step(arc_ctx* c, const arc_model_config* mc, int64_t t, con
   o.fN = static_cast<float>(c->N);
   const bool vec = c->d % 4 == 0 && aligned16(G) && aligned16(x) &&
                    (o.kind < 1 || aligned16(opt_m)) && (o.kind < 2 || aligned16(opt_v));
+  if (dense) {
+    if (vec && aligned16(grad) && aligned16(h) && aligned16(g)) {
+      ARC_HIP(arc::launch_dense_model(c->lds_per_cu == arc::kLdsPerCu, o, grad, c->grad_bf16, h, g, G,
+                                      x, opt_m, opt_v, c->d, c->N, c->eta, c->a, c->stream),
+              "dense model step launch");
+      return ARC_OK;
+    }
+    ARC_HIP(arc::launch_dense_step(grad, c->grad_bf16, h, g, G, c->d, c->N, c->eta, c->a,
+                                   c->stream),
+            "dense step launch");
+  } else {
+    st = arc::enqueue_step(c, t, grad, h, g, out_idx, out_agg, G);
+    if (st != ARC_OK) return st;
+  }
   ARC_HIP(arc::launch_optimizer(vec, c->lds_per_cu == arc::kLdsPerCu, o, G, x, opt_m, opt_v,
                                 c->d, c->stream),
           "optimizer launch");

@@ -175,7 +175,8 @@ hipError_t launch_row_norms(int32_t group_rows, bool unaligned, const void* grad
 
 // ---- comparison compressors (arc_compare.hip) ----
 
-// Eq. (11a) alone over all N*d coordinates (Rand-K needs no residual pass).
+// Eq. (11a) alone over all N*d coordinates (Rand-K needs no residual pass);
+// vec: 16-byte aligned arrays.
 hipError_t launch_momentum(bool vec, const void* grad, int32_t grad_bf16, float* h,
                            int64_t count, float eta, float a, hipStream_t stream);
 
@@ -232,13 +233,6 @@ hipError_t launch_gather_update_tensors(const float* h, float* g,
                                         int64_t total_work, int64_t d, int32_t N,
                                         hipStream_t stream);
 
-// Model step (arc_model.hip).  Dense step: Eq. (11a), (11b) with the identity
-// compressor, payload added into G, every coordinate (vec: 16-byte aligned
-// pointers and d % 4 == 0).
-hipError_t launch_dense_step(bool vec, const void* grad, int32_t grad_bf16, float* h,
-                             float* g, float* G, int64_t d, int32_t N, float eta, float a,
-                             hipStream_t stream);
-
 // Optimiser constants of one x update (host-computed).
 struct OptimizerArgs {
   int32_t kind;        // 0 SGD, 1 MSGD, 2 Adam
@@ -250,6 +244,17 @@ struct OptimizerArgs {
   float eps, weight_decay;
   float fN;            // number of nodes
 };
+
+// Model step (arc_model.hip).  Dense step: Eq. (11a), (11b) with the identity
+// compressor, payload added into G, every coordinate; any alignment.
+hipError_t launch_dense_step(const void* grad, int32_t grad_bf16, float* h, float* g, float* G,
+                             int64_t d, int32_t N, float eta, float a, hipStream_t stream);
+
+// The dense step and the x update after it in one pass: 16-byte aligned
+// arrays and d % 4 == 0; cap as for launch_optimizer.
+hipError_t launch_dense_model(bool cap, const OptimizerArgs& o, const void* grad, int32_t grad_bf16,
+                              float* h, float* g, float* G, float* x, float* m, float* v,
+                              int64_t d, int32_t N, float eta, float a, hipStream_t stream);
 
 // x (and m, v) updated from G over every coordinate.  vec: 16-byte aligned
 // arrays and d % 4 == 0; cap: the device has the MI355X's 160 KB of LDS per

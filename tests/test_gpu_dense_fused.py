@@ -1,0 +1,37 @@
+"""GPU parity of the dense iteration with its x update in one pass: worker
+counts around the batch of four, every optimiser, both gradient types, the
+sizes of a partial last workgroup, and the two-pass path off 16 bytes; and of
+Rand-K's momentum where N * d is not a multiple of four."""
+import pytest
+import torch
+
+from parity_util import log
+from test_gpu_model import run_model_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+@pytest.mark.parametrize("N", [1, 3, 4, 5, 8, 9])
+@pytest.mark.parametrize("optimizer", ["sgd", "msgd", "adam"])
+def test_dense_iterations(N, optimizer):
+    for d, dtype, mis in ((4, "f32", 0), (1024 * 4, "bf16", 0), (1024 * 9 + 36, "f32", 0),
+                          (5000 + 3, "bf16", 0), (4096, "f32", 1)):
+        log(f"[dense] N={N} {optimizer} d={d} {dtype} misalign={mis}")
+        run_model_case(label=f"dense_{N}_{optimizer}_{d}", d=d, N=N, n=4, K=1, steps=3,
+                       dense_steps=2, optimizer=optimizer, grad_dtype=dtype,
+                       family=1 if dtype == "bf16" else 0, weight_decay=5e-4, misalign=mis)
+
+
+@pytest.mark.parametrize("d,N", [(1, 1), (3, 1), (4097, 3), (2051, 2), (1023, 5), (1024, 3)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_randk_momentum_of_any_length(d, N, dtype):
+    log(f"[dense] randk momentum d={d} N={N} {dtype}")
+    run_model_case(label=f"randk_{d}_{N}", d=d, N=N, n=5, K=1, steps=2, dense_steps=0,
+                   optimizer="sgd", compressor="randk", grad_dtype=dtype,
+                   family=1 if dtype == "bf16" else 0)
