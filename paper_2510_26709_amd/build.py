@@ -14,9 +14,10 @@ OBJ_DIR = os.path.join(HERE, "_build")
 
 # Strict binary32 semantics (no contraction beyond explicit fmaf, no fast-math,
 # denormals kept, correctly rounded division and square root) and no
-# packed-FP32 instructions.
+# packed-FP32 instructions.  Host square roots need not set errno, so that
+# loops over them vectorise.
 HIP_FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17",
-             "-ffp-contract=off", "-fno-fast-math", "-fhip-fp32-correctly-rounded-divide-sqrt",
+             "-ffp-contract=off", "-fno-fast-math", "-fno-math-errno", "-fhip-fp32-correctly-rounded-divide-sqrt",
              "-Wall", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 

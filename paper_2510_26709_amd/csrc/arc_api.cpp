@@ -528,7 +528,7 @@ arc_status record(arc_ctx* c, size_t slot, int which) {
   return ARC_OK;
 }
 
-// Host threads for the projection: one per 8K values (a few hundred
+// Host threads for the projection: one per 8K values (about a hundred
 // microseconds of Box-Muller each, well under a step of the device), at most
 // 8 and at most half the cores.
 int projection_threads(int64_t v_floats) {

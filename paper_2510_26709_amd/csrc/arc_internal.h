@@ -270,6 +270,11 @@ void generate_projection(uint64_t seed, int64_t t, int64_t n, int32_t r,
 void generate_projection_rows(uint64_t seed, int64_t t, int64_t n, int32_t r, int64_t j0,
                               int64_t j1, float* V);
 
+// out[k] = binary32 of sqrt(-2 ln u1[k]) cos(2 pi u2[k]), the C library's bits,
+// for n <= kBoxMullerBlock pairs, u1 in (0, 1], u2 in [0, 1).
+constexpr int kBoxMullerBlock = 64;
+void box_muller_block(const double* u1, const double* u2, int n, float* out);
+
 // One width's V_t inside a staging buffer: `width` rows of r floats at
 // float offset `offset`.
 struct ProjectionBlock {
