@@ -377,27 +377,41 @@ void build_node_selection(const std::vector<int64_t>& begin, const std::vector<i
 }
 
 // Lowers the configuration to the kernels' tables (host side only).
-void build_plan(const arc_config* cfg, arc_ctx* c) {
+void build_plan(const arc_config* cfg, arc::PlanKind kind, arc_ctx* c) {
   GroupLists lists;
   std::vector<int64_t> begin{0}, want;
   // r in {1,2,4,8} for the vectorised sketch; the other compressors use no V.
   const bool r_ok = c->compressor != ARC_COMP_ARC || vector_r(c->r);
+  // Row groups' size for the vectorised kernels under this kind of plan.
+  const auto group_rows = [&](bool aligned, int64_t cols) {
+    if (!r_ok || kind == arc::PlanKind::kGeneral ||
+        (kind == arc::PlanKind::kAlignedWindows && !aligned))
+      return 0;
+    return vector_group_rows(cols);
+  };
+  // V_t of every width starts on 16 bytes and is read as whole float4s (the
+  // general kernel needs neither).
+  const auto padded = [&](int64_t floats) {
+    return kind == arc::PlanKind::kGeneral ? floats : (floats + 3) / 4 * 4;
+  };
   if (!c->tensor_mode) {
     // One m x n view (Eq. (3)); rows [0, m_full) are whole, row m_full (if
     // any) holds the d - m_full*n remaining coordinates.
     c->widths.push_back(c->n);
     c->v_off[c->n] = 0;
-    c->v_floats = (c->n * c->r + 3) / 4 * 4;  // read as whole float4s
+    c->v_floats = padded(c->n * c->r);
     const int64_t m_full = c->d / c->n;
-    const int32_t gr = r_ok ? vector_group_rows(c->n) : 0;
+    const bool aligned = c->d % 4 == 0 && c->n % 4 == 0;
+    const int32_t gr = group_rows(aligned, c->n);
     if (gr > 0) {
       // The ragged row is a one-row group as wide as its values, in the same
       // launch as the others.
-      const bool aligned = c->d % 4 == 0 && c->n % 4 == 0;
       // Rows on 16 bytes that all start the same distance past a line keep
       // the window kernels' common shift where they are wide.
       const bool on_lines = c->n % 32 == 0 && (c->d % 32 == 0 || (aligned && c->n > kSpanMaxCols));
-      const RowKernel kernel = on_lines ? RowKernel::kWindow : off_line_kernel(m_full, c->n);
+      const RowKernel kernel = on_lines || kind != arc::PlanKind::kFast
+                                   ? RowKernel::kWindow
+                                   : off_line_kernel(m_full, c->n);
       const int64_t tail = c->d - m_full * c->n;
       add_groups(0, 0, m_full, c->n, c->n, 0, kernel, gr, aligned, &lists);
       if (tail > 0)
@@ -440,7 +454,7 @@ void build_plan(const arc_config* cfg, arc_ctx* c) {
       const int64_t w = cfg->tensors[b].cols;
       if (c->v_off.emplace(w, c->v_floats).second) {
         c->widths.push_back(w);
-        c->v_floats += (w * c->r + 3) / 4 * 4;  // every V_t starts on 16 bytes
+        c->v_floats += padded(w * c->r);
       }
     }
     int64_t off = 0, row0 = 0;
@@ -450,7 +464,7 @@ void build_plan(const arc_config* cfg, arc_ctx* c) {
       // Tensors on 16 bytes keep the window kernels, whose launches they
       // share (per-tensor ResNet-18 377 us, 382 with its rows off the lines
       // in the span and lines kernels).
-      const int32_t gr = r_ok ? vector_group_rows(t.cols) : 0;
+      const int32_t gr = group_rows(aligned, t.cols);
       const RowKernel kernel = gr == 0   ? RowKernel::kGeneral
                                : aligned ? RowKernel::kWindow
                                          : off_line_kernel(t.rows, t.cols);
@@ -622,7 +636,7 @@ arc_status arc_create(const arc_config* cfg, void* hip_stream, arc_ctx** out) {
 
   arc_ctx* c = new (std::nothrow) arc_ctx();
   if (c == nullptr) return fail(ARC_ERR_NOMEM, "host allocation failed");
-  st = arc::plan_context(cfg, m, hip_stream, c);
+  st = arc::plan_context(cfg, m, hip_stream, arc::PlanKind::kFast, c);
   if (st != ARC_OK) {
     delete c;
     return st;
@@ -1162,7 +1176,8 @@ arc_status arc_timing_read(arc_ctx* c, double* ms, int64_t* steps) {
 
 namespace arc {
 
-arc_status plan_context(const arc_config* cfg, int64_t m, void* stream, arc_ctx* c) {
+arc_status plan_context(const arc_config* cfg, int64_t m, void* stream, PlanKind kind,
+                        arc_ctx* c) {
   try {
     c->d = cfg->d;
     c->tensor_mode = cfg->num_tensors > 0;
@@ -1176,7 +1191,7 @@ arc_status plan_context(const arc_config* cfg, int64_t m, void* stream, arc_ctx*
     c->a = 1.0f - cfg->eta;
     c->seed = cfg->seed;
     c->stream = static_cast<hipStream_t>(stream);
-    build_plan(cfg, c);
+    build_plan(cfg, kind, c);
   } catch (...) {
     return fail(ARC_ERR_NOMEM, "host allocation failed");
   }

@@ -182,10 +182,16 @@ namespace arc {
 // Checks cfg (no HIP call); on success *m_out is the number of rows.
 arc_status check_config(const arc_config* cfg, int64_t* m_out);
 
+// Which streaming kernels a plan may use: all of them; the window kernels on
+// rows that lie on 16 bytes and the general kernel elsewhere; or the general
+// kernel alone, whose tables are the smallest.
+enum class PlanKind { kFast, kAlignedWindows, kGeneral };
+
 // Fills the context's problem fields and lowers cfg (already checked, m
 // rows) to the kernels' host tables; binds the context to `stream`.  Host
 // work only.
-arc_status plan_context(const arc_config* cfg, int64_t m, void* stream, arc_ctx* c);
+arc_status plan_context(const arc_config* cfg, int64_t m, void* stream, PlanKind kind,
+                        arc_ctx* c);
 
 // The current device, its LDS limit and the launch shapes that depend on
 // it (no allocation).

@@ -1,7 +1,8 @@
 // General sketch kernel: the same streaming stage as the vectorised kernels
 // (EF21M momentum (11a), Delta = h_t - g_{t-1}, per-worker sketch of Alg. 1)
 // for row groups those cannot take: r other than 1, 2, 4 and 8 (up to
-// ARC_MAX_R), and rows of more than 2^22 values.  Any element alignment, and
+// ARC_MAX_R), rows of more than 2^22 values, and plans that need the smallest
+// tables.  Any element alignment, and
 // a ragged last row.
 //
 // One wave per (row group, worker).

@@ -14,6 +14,7 @@
 
 #include <cstring>
 #include <mutex>
+#include <optional>
 #include <vector>
 
 #include "arc_context.h"
@@ -113,10 +114,20 @@ extern "C" arc_status arc_step_static(const arc_config* cfg, void* hip_stream, i
   arc_status st = arc::check_config(cfg, &m);
   if (st != ARC_OK) return st;
   // Host tables only: its device pointers are set into the scratch array
-  // below, and it is never released.
-  arc_ctx c;
-  if ((st = arc::plan_context(cfg, m, hip_stream, &c)) != ARC_OK) return st;
-  const Layout L = layout_of(c);
+  // below, and it is never released.  The fastest kernels take up to eight
+  // times the row groups of the general ones (5 rows a group instead of 64 at
+  // 819 values), so a configuration whose tables do not fit with them is
+  // planned with fewer: windows for the aligned rows alone, then none.
+  std::optional<arc_ctx> plan;
+  Layout L{};
+  for (const arc::PlanKind kind : {arc::PlanKind::kFast, arc::PlanKind::kAlignedWindows,
+                                   arc::PlanKind::kGeneral}) {
+    plan.emplace();
+    if ((st = arc::plan_context(cfg, m, hip_stream, kind, &*plan)) != ARC_OK) return st;
+    L = layout_of(*plan);
+    if (L.total <= ARC_STATIC_SCRATCH_BYTES) break;
+  }
+  arc_ctx& c = *plan;
   if (L.total > ARC_STATIC_SCRATCH_BYTES)
     return arc::fail(ARC_ERR_INVALID,
                      "arc_step_static: this configuration needs " + std::to_string(L.total) +

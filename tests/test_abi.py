@@ -232,3 +232,26 @@ def test_static_step_rejects_before_any_device_work():
     assert "static" in msg and str(arc.ARC_STATIC_SCRATCH_BYTES) in msg, msg
     with pytest.raises(arc.ArcError, match="static"):
         arc.arc_step_static(cfg, None, 0, 1, 2, 3, 4, 5)
+
+
+@pytest.mark.parametrize("d,kw", [
+    # r = 1, one worker, 819-wide rows at any alignment (5 rows a group in the
+    # span kernel) and 608-wide ones off the 128-byte lines (6, 64 a window
+    # group); wide rows (8 a group, 64 in the general kernel).
+    (6_900_000 * 819, dict(n=819)),
+    (6_900_000 * 608 + 4, dict(n=608)),
+    (6_900_000 * 1001, dict(n=1001)),
+    # per tensor, at an odd offset
+    (6_900_000 * 801 + 3, dict(tensors=[(1, 3, 1), (6_900_000, 801, 1)])),
+])
+def test_static_step_accepts_what_fits_with_the_smallest_tables(d, kw):
+    """The sketch and importances of 6.9e6 rows take 55.2 of the static
+    67.1 MB; row groups of the fastest kernels would take 35 to 55 MB more, so
+    the call plans with the kernels whose tables are smaller.  It then gets as
+    far as the pointers, all NULL here (no GPU is needed)."""
+    if "n" in kw:
+        kw = dict(kw, K=1)
+    cfg, keep = arc.make_config(**dict(kw, d=d, N=1, r=1, eta=0.1, seed=1))
+    assert _lib._lib.arc_step_static(ctypes.byref(cfg), None, 0, None, None, None, None,
+                                     None) == arc.ARC_ERR_INVALID
+    assert "NULL" in arc.arc_last_error(), arc.arc_last_error()
