@@ -1032,12 +1032,17 @@ arc_status arc_model_step(arc_ctx* c, const arc_model_config* mc, int64_t t, con
   o.eps = mc->eps;
   o.weight_decay = mc->weight_decay;
   o.fN = static_cast<float>(c->N);
-  const bool vec = c->d % 4 == 0 && aligned16(G) && aligned16(x) &&
-                   (o.kind < 1 || aligned16(opt_m)) && (o.kind < 2 || aligned16(opt_v));
+  const bool cap = c->lds_per_cu == arc::kLdsPerCu;
+  const bool aligned = c->d % 4 == 0 && aligned16(G) && aligned16(x) &&
+                       (o.kind < 1 || aligned16(opt_m)) && (o.kind < 2 || aligned16(opt_v));
   if (dense) {
-    if (vec && aligned16(grad) && aligned16(h) && aligned16(g)) {
-      ARC_HIP(arc::launch_dense_model(c->lds_per_cu == arc::kLdsPerCu, o, grad, c->grad_bf16, h, g, G,
-                                      x, opt_m, opt_v, c->d, c->N, c->eta, c->a, c->stream),
+    // Where the workers' arrays lie on 16 bytes, one pass; else the x update
+    // reads G again (one pass at word alignment: 3 bf16 workers of 6.0e7 values
+    // with Adam as long as one value a lane in two passes, 8 binary32 workers
+    // of 1.2e7 4% longer).
+    if (c->d % 4 == 0 && aligned16(grad) && aligned16(h) && aligned16(g)) {
+      ARC_HIP(arc::launch_dense_model(aligned, cap, o, grad, c->grad_bf16, h, g, G, x, opt_m,
+                                      opt_v, c->d, c->N, c->eta, c->a, c->stream),
               "dense model step launch");
       return ARC_OK;
     }
@@ -1048,8 +1053,7 @@ arc_status arc_model_step(arc_ctx* c, const arc_model_config* mc, int64_t t, con
     st = arc::enqueue_step(c, t, grad, h, g, out_idx, out_agg, G);
     if (st != ARC_OK) return st;
   }
-  ARC_HIP(arc::launch_optimizer(vec, c->lds_per_cu == arc::kLdsPerCu, o, G, x, opt_m, opt_v,
-                                c->d, c->stream),
+  ARC_HIP(arc::launch_optimizer(aligned, cap, o, G, x, opt_m, opt_v, c->d, c->stream),
           "optimizer launch");
   return ARC_OK;
 }

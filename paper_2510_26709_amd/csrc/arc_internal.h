@@ -250,17 +250,19 @@ struct OptimizerArgs {
 hipError_t launch_dense_step(const void* grad, int32_t grad_bf16, float* h, float* g, float* G,
                              int64_t d, int32_t N, float eta, float a, hipStream_t stream);
 
-// The dense step and the x update after it in one pass: 16-byte aligned
-// arrays and d % 4 == 0; cap as for launch_optimizer.
-hipError_t launch_dense_model(bool cap, const OptimizerArgs& o, const void* grad, int32_t grad_bf16,
-                              float* h, float* g, float* G, float* x, float* m, float* v,
-                              int64_t d, int32_t N, float eta, float a, hipStream_t stream);
+// The dense step and the x update after it in one pass: grad, h and g 16-byte
+// aligned and d % 4 == 0; aligned: G, x, m and v 16-byte aligned too; cap as for
+// launch_optimizer.
+hipError_t launch_dense_model(bool aligned, bool cap, const OptimizerArgs& o, const void* grad,
+                              int32_t grad_bf16, float* h, float* g, float* G, float* x, float* m,
+                              float* v, int64_t d, int32_t N, float eta, float a,
+                              hipStream_t stream);
 
-// x (and m, v) updated from G over every coordinate.  vec: 16-byte aligned
-// arrays and d % 4 == 0; cap: the device has the MI355X's 160 KB of LDS per
-// compute unit, used to cap the vectorised launch's occupancy.
-hipError_t launch_optimizer(bool vec, bool cap, const OptimizerArgs& o, const float* G, float* x,
-                            float* m, float* v, int64_t d, hipStream_t stream);
+// x (and m, v) updated from G over every coordinate, at any element alignment.
+// aligned: 16-byte aligned arrays and d % 4 == 0; cap: the device has the
+// MI355X's 160 KB of LDS per compute unit, used to cap the launch's occupancy.
+hipError_t launch_optimizer(bool aligned, bool cap, const OptimizerArgs& o, const float* G, float* x, float* m,
+                            float* v, int64_t d, hipStream_t stream);
 
 // ---- host projection (arc_projection.cpp) ----
 // V_t (n x r, row-major) for the shared seed and step t.

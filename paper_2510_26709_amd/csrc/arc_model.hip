@@ -60,6 +60,19 @@ __device__ __forceinline__ void update_one(const OptimizerArgs& o, float Gi, flo
 // one worker, Adam, 1.87 -> 1.74; 4.0e7 binary32 of 8 workers, heavy ball,
 // 1.40 -> 1.38.
 // ---------------------------------------------------------------------------
+// Four values on 16 bytes, or (W) at any word.
+template <bool W>
+__device__ __forceinline__ float4 load4(const float* p) {
+  if constexpr (W) return load_f4_words(p);
+  return stream_load(reinterpret_cast<const float4*>(p));
+}
+template <bool W>
+__device__ __forceinline__ void store4(float* p, float4 v) {
+  if constexpr (W)
+    store_f4_words(p, v);
+  else
+    stream_store(reinterpret_cast<float4*>(p), v);
+}
 template <bool BF16>
 __device__ __forceinline__ float4 load_grad4(const void* grad, int64_t at) {
   if constexpr (BF16) {
@@ -75,7 +88,7 @@ constexpr int kDenseWorkers = 4;
 // unit (of the MI355X's 160 KB).
 constexpr size_t kDenseLdsCap = 80 * 1024;
 
-template <bool BF16, int KIND>
+template <bool BF16, int KIND, bool W>
 __global__ void __launch_bounds__(256)
 dense_model_vec_kernel(const void* __restrict__ grad, float* __restrict__ h,
                        float* __restrict__ g, float* __restrict__ G, OptimizerArgs o,
@@ -83,11 +96,11 @@ dense_model_vec_kernel(const void* __restrict__ grad, float* __restrict__ h,
                        int64_t d, int32_t N, float eta, float a) {
   const int64_t e = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
   if (e >= d) return;
-  float4 Gv = stream_load(reinterpret_cast<const float4*>(G + e));
-  float4 xv = stream_load(reinterpret_cast<const float4*>(x + e));
+  float4 Gv = load4<W>(G + e);
+  float4 xv = load4<W>(x + e);
   float4 mv = make_float4(0.f, 0.f, 0.f, 0.f), vv = mv, acc = mv;
-  if constexpr (KIND >= 1) mv = stream_load(reinterpret_cast<const float4*>(m + e));
-  if constexpr (KIND == 2) vv = stream_load(reinterpret_cast<const float4*>(v + e));
+  if constexpr (KIND >= 1) mv = load4<W>(m + e);
+  if constexpr (KIND == 2) vv = load4<W>(v + e);
   for (int32_t i0 = 0; i0 < N; i0 += kDenseWorkers) {
     float4 gr[kDenseWorkers], hv[kDenseWorkers], gv[kDenseWorkers];
 #pragma unroll
@@ -95,8 +108,8 @@ dense_model_vec_kernel(const void* __restrict__ grad, float* __restrict__ h,
       if (i0 + u < N) {
         const int64_t at = (int64_t)(i0 + u) * d + e;
         gr[u] = load_grad4<BF16>(grad, at);
-        hv[u] = stream_load(reinterpret_cast<const float4*>(h + at));
-        gv[u] = stream_load(reinterpret_cast<const float4*>(g + at));
+        hv[u] = load4<false>(h + at);
+        gv[u] = load4<false>(g + at);
       }
     }
 #pragma unroll
@@ -117,9 +130,8 @@ dense_model_vec_kernel(const void* __restrict__ grad, float* __restrict__ h,
           acc.z = acc.z + dl.z;
           acc.w = acc.w + dl.w;
         }
-        stream_store(reinterpret_cast<float4*>(h + at), hv[u]);
-        stream_store(reinterpret_cast<float4*>(g + at),
-                     make_float4(gv[u].x + dl.x, gv[u].y + dl.y, gv[u].z + dl.z,
+        store4<false>(h + at, hv[u]);
+        store4<false>(g + at, make_float4(gv[u].x + dl.x, gv[u].y + dl.y, gv[u].z + dl.z,
                                  gv[u].w + dl.w));
       }
     }
@@ -132,10 +144,10 @@ dense_model_vec_kernel(const void* __restrict__ grad, float* __restrict__ h,
   update_one<KIND>(o, Gv.y, xv.y, mv.y, vv.y);
   update_one<KIND>(o, Gv.z, xv.z, mv.z, vv.z);
   update_one<KIND>(o, Gv.w, xv.w, mv.w, vv.w);
-  stream_store(reinterpret_cast<float4*>(G + e), Gv);
-  stream_store(reinterpret_cast<float4*>(x + e), xv);
-  if constexpr (KIND >= 1) stream_store(reinterpret_cast<float4*>(m + e), mv);
-  if constexpr (KIND == 2) stream_store(reinterpret_cast<float4*>(v + e), vv);
+  store4<W>(G + e, Gv);
+  store4<W>(x + e, xv);
+  if constexpr (KIND >= 1) store4<W>(m + e, mv);
+  if constexpr (KIND == 2) store4<W>(v + e, vv);
 }
 
 __global__ void __launch_bounds__(256)
@@ -161,9 +173,10 @@ dense_step_scalar_kernel(const void* __restrict__ grad, int32_t grad_bf16,
 
 // Vectorised x update: one workgroup of 256 threads per tile of kOptTile
 // coordinates, each thread kOptUnroll float4 of every array (all loads of a
-// thread in flight together), through buffer resources that end at d: the
-// hardware returns zero for loads past the end and drops those stores, so the
-// last, partial tile needs no branch.  Loads are non-temporal (every value is
+// thread in flight together), through buffer resources that end with
+// d's last whole quad: the hardware returns zero for loads past the end and
+// drops those stores, so the last, partial tile needs no branch; the last
+// d % 4 coordinates go one a thread.  Arrays need whole words only.  Loads are non-temporal (every value is
 // read once), stores non-temporal at device scope (read again only by later
 // launches).  Adam over 1.1e9 coordinates (28 bytes each), three MI355X
 // boxes, every variant in one process per box: one float4 per thread
@@ -183,7 +196,17 @@ optimizer_vec_kernel(OptimizerArgs o, const float* __restrict__ G, float* __rest
                      float* __restrict__ m, float* __restrict__ v, int64_t d) {
   const int64_t b0 = (int64_t)blockIdx.x * kOptTile;
   const int64_t left = d - b0;
-  const uint32_t bytes = (uint32_t)(left < kOptTile ? left : kOptTile) * 4u;
+  if (left <= kOptTile && (int64_t)threadIdx.x < (d & 3)) {
+    const int64_t e = d - (d & 3) + threadIdx.x;
+    float xe = x[e], me = 0.0f, ve = 0.0f;
+    if constexpr (KIND >= 1) me = m[e];
+    if constexpr (KIND == 2) ve = v[e];
+    update_one<KIND>(o, G[e], xe, me, ve);
+    x[e] = xe;
+    if constexpr (KIND >= 1) m[e] = me;
+    if constexpr (KIND == 2) v[e] = ve;
+  }
+  const uint32_t bytes = (uint32_t)(left < kOptTile ? left / 4 * 4 : kOptTile) * 4u;
   const buffer_rsrc rG = make_buffer(G + b0, bytes);
   const buffer_rsrc rx = make_buffer(x + b0, bytes);
   const buffer_rsrc rm = make_buffer(KIND >= 1 ? m + b0 : x + b0, bytes);
@@ -211,35 +234,26 @@ optimizer_vec_kernel(OptimizerArgs o, const float* __restrict__ G, float* __rest
   }
 }
 
-template <int KIND>
+// Adam where an array is off 16 bytes or d % 4 != 0, one coordinate a thread:
+// the tiles above take as long at 5.0e7 coordinates (bf16 step 417 / 418 us)
+// and 0.7 us longer at 3.0e5; SGD and heavy ball gain there (5.0e7
+// coordinates with SGD 307 -> 271 us a step, per-tensor CIFAR ResNet-18 with
+// heavy ball 260 -> 250).
 __global__ void __launch_bounds__(256)
-optimizer_scalar_kernel(OptimizerArgs o, const float* __restrict__ G, float* __restrict__ x,
-                        float* __restrict__ m, float* __restrict__ v, int64_t d) {
+adam_scalar_kernel(OptimizerArgs o, const float* __restrict__ G, float* __restrict__ x,
+                   float* __restrict__ m, float* __restrict__ v, int64_t d) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= d) return;
-  float xe = x[e], me = 0.0f, ve = 0.0f;
-  if constexpr (KIND >= 1) me = m[e];
-  if constexpr (KIND == 2) ve = v[e];
-  update_one<KIND>(o, G[e], xe, me, ve);
+  float xe = x[e], me = m[e], ve = v[e];
+  update_one<2>(o, G[e], xe, me, ve);
   x[e] = xe;
-  if constexpr (KIND >= 1) m[e] = me;
-  if constexpr (KIND == 2) v[e] = ve;
+  m[e] = me;
+  v[e] = ve;
 }
 
 // Dynamic LDS that caps the vectorised update at four workgroups per compute
 // unit (of the MI355X's 160 KB).
 constexpr size_t kOptLdsCap = 36 * 1024;
-
-template <int KIND>
-void launch_optimizer_kind(bool vec, bool cap, const OptimizerArgs& o, const float* G, float* x,
-                           float* m, float* v, int64_t d, hipStream_t stream) {
-  if (vec)
-    hipLaunchKernelGGL(optimizer_vec_kernel<KIND>, dim3(blocks_for(d, kOptTile)), dim3(256),
-                       cap ? kOptLdsCap : 0, stream, o, G, x, m, v, d);
-  else
-    hipLaunchKernelGGL(optimizer_scalar_kernel<KIND>, dim3(blocks_for(d, 256)), dim3(256), 0,
-                       stream, o, G, x, m, v, d);
-}
 
 }  // namespace
 
@@ -251,39 +265,61 @@ hipError_t launch_dense_step(const void* grad, int32_t grad_bf16, float* h, floa
   return hipGetLastError();
 }
 
-hipError_t launch_dense_model(bool cap, const OptimizerArgs& o, const void* grad, int32_t grad_bf16,
-                              float* h, float* g, float* G, float* x, float* m, float* v,
-                              int64_t d, int32_t N, float eta, float a, hipStream_t stream) {
+hipError_t launch_dense_model(bool aligned, bool cap, const OptimizerArgs& o, const void* grad,
+                              int32_t grad_bf16, float* h, float* g, float* G, float* x, float* m,
+                              float* v, int64_t d, int32_t N, float eta, float a,
+                              hipStream_t stream) {
   if (d <= 0) return hipSuccess;
-  const dim3 grid(blocks_for((d + 3) / 4, 256));
+  const dim3 grid(blocks_for(d / 4, 256));
   const size_t lds = cap ? kDenseLdsCap : 0;
-#define ARC_DENSE(KK)                                                                          \
-  if (grad_bf16)                                                                               \
-    hipLaunchKernelGGL((dense_model_vec_kernel<true, KK>), grid, dim3(256), lds, stream, grad,   \
-                       h, g, G, o, x, m, v, d, N, eta, a);                                     \
-  else                                                                                         \
-    hipLaunchKernelGGL((dense_model_vec_kernel<false, KK>), grid, dim3(256), lds, stream, grad,  \
-                       h, g, G, o, x, m, v, d, N, eta, a)
+#define ARC_DENSE_W(BB, KK, WW)                                                                \
+  hipLaunchKernelGGL((dense_model_vec_kernel<BB, KK, WW>), grid, dim3(256), lds, stream, grad, \
+                     h, g, G, o, x, m, v, d, N, eta, a)
+#define ARC_DENSE(KK)                     \
+  if (grad_bf16) {                        \
+    if (aligned)                          \
+      ARC_DENSE_W(true, KK, false);       \
+    else                                  \
+      ARC_DENSE_W(true, KK, true);        \
+  } else {                                \
+    if (aligned)                          \
+      ARC_DENSE_W(false, KK, false);      \
+    else                                  \
+      ARC_DENSE_W(false, KK, true);       \
+  }                                       \
+  break
   switch (o.kind) {
-    case 0: ARC_DENSE(0); break;
-    case 1: ARC_DENSE(1); break;
-    case 2: ARC_DENSE(2); break;
+    case 0: ARC_DENSE(0);
+    case 1: ARC_DENSE(1);
+    case 2: ARC_DENSE(2);
     default: return hipErrorInvalidValue;
   }
 #undef ARC_DENSE
+#undef ARC_DENSE_W
   return hipGetLastError();
 }
 
-hipError_t launch_optimizer(bool vec, bool cap, const OptimizerArgs& o, const float* G, float* x,
-                            float* m, float* v, int64_t d, hipStream_t stream) {
+hipError_t launch_optimizer(bool aligned, bool cap, const OptimizerArgs& o, const float* G, float* x, float* m,
+                            float* v, int64_t d, hipStream_t stream) {
   if (d <= 0) return hipSuccess;
-  if (vec && d > INT64_MAX - kOptTile) return hipErrorInvalidValue;
+  if (d > INT64_MAX - kOptTile) return hipErrorInvalidValue;
+  const dim3 grid(blocks_for(d, kOptTile));
+  const size_t lds = cap ? kOptLdsCap : 0;
+#define ARC_OPT(KK)                                                                          \
+  hipLaunchKernelGGL(optimizer_vec_kernel<KK>, grid, dim3(256), lds, stream, o, G, x, m, v, d)
   switch (o.kind) {
-    case 0: launch_optimizer_kind<0>(vec, cap, o, G, x, m, v, d, stream); break;
-    case 1: launch_optimizer_kind<1>(vec, cap, o, G, x, m, v, d, stream); break;
-    case 2: launch_optimizer_kind<2>(vec, cap, o, G, x, m, v, d, stream); break;
+    case 0: ARC_OPT(0); break;
+    case 1: ARC_OPT(1); break;
+    case 2:
+      if (aligned)
+        ARC_OPT(2);
+      else
+        hipLaunchKernelGGL(adam_scalar_kernel, dim3(blocks_for(d, 256)), dim3(256), 0, stream, o,
+                           G, x, m, v, d);
+      break;
     default: return hipErrorInvalidValue;
   }
+#undef ARC_OPT
   return hipGetLastError();
 }
 

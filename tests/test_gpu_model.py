@@ -25,7 +25,8 @@ def _gpu():
 def run_model_case(*, d, N, n=0, tensors=None, r=4, K=0, eta=0.1, seed=3, grad_dtype="f32",
                    family=0, optimizer="adam", steps=4, dense_steps=1, lr=1e-2, momentum=0.9,
                    beta1=0.9, beta2=0.999, eps=1e-8, weight_decay=0.0, misalign=0,
-                   compressor="arc", label="model"):
+                   misalign_model=None, compressor="arc", label="model"):
+    mis_model = misalign if misalign_model is None else misalign_model
     dev = torch.device("cuda:0")
     sizes = None if tensors is None else [a * b for a, b, _ in tensors]
     gen = synth.Generator(d, N, 21, grad_dtype=grad_dtype, family=family, tensors=sizes)
@@ -36,10 +37,10 @@ def run_model_case(*, d, N, n=0, tensors=None, r=4, K=0, eta=0.1, seed=3, grad_d
     try:
         h = device_buffer((N, d), torch.float32, dev, misalign)
         g = device_buffer((N, d), torch.float32, dev, misalign)
-        G = device_buffer((d,), torch.float32, dev, misalign)
-        x = device_buffer((d,), torch.float32, dev, misalign)
-        m = device_buffer((d,), torch.float32, dev, misalign)
-        v = device_buffer((d,), torch.float32, dev, misalign)
+        G = device_buffer((d,), torch.float32, dev, mis_model)
+        x = device_buffer((d,), torch.float32, dev, mis_model)
+        m = device_buffer((d,), torch.float32, dev, mis_model)
+        v = device_buffer((d,), torch.float32, dev, mis_model)
         rng = np.random.default_rng(8)
         x0 = rng.standard_normal(d).astype(F32)
         x.copy_(torch.from_numpy(x0))
