@@ -509,10 +509,12 @@ void build_plan(const arc_config* cfg, arc::PlanKind kind, arc_ctx* c) {
     c->groups.insert(c->groups.end(), lists.vec[sz].begin(), lists.vec[sz].end());
   }
   c->nvec_groups = static_cast<int64_t>(c->groups.size());
-  for (const arc::RowGroup& grp : lists.vec[arc::kSpanList])
+  for (const arc::RowGroup& grp : lists.vec[arc::kSpanList]) {
     c->span_floats = std::max(
         c->span_floats, arc::span_wave_floats(grp.rows, grp.cols,
                                               c->compressor == ARC_COMP_ARC ? c->r : 0));
+    c->span_values = std::max(c->span_values, grp.rows * grp.cols);
+  }
   c->groups.insert(c->groups.end(), lists.general.begin(), lists.general.end());
   for (const arc::RowGroup& grp : lists.general)
     c->stage_elems[arc::kVecLists] += (grp.rows - 1) * static_cast<int64_t>(grp.cols) + grp.last_len;
@@ -821,7 +823,7 @@ arc_status launch_streaming_stage(arc_ctx* c, const void* grad, float* h, const 
       if (w == arc::kSpanList) {
         ARC_HIP(arc::launch_sketch_span(grad, c->grad_bf16, h, g, c->V_dev, grp, c->vec_count[w],
                                         c->S_dev, c->d, c->m, c->N, norm ? 1 : c->r, c->eta,
-                                        c->a, norm, c->span_floats, s),
+                                        c->a, norm, c->span_floats, c->span_values, s),
                 "sketch launch (narrow rows)");
         continue;
       }
@@ -1084,7 +1086,7 @@ arc_status arc_describe(const arc_ctx* c, char* buf, int64_t len) {
                 "compressor=%s mode=%s sketch=%s widths=%zu row_groups=%lld vector_groups=%lld "
                 "(64:%lld 32:%lld 16:%lld 8:%lld rows) workgroup_waves=(%d%s %d%s %d%s %d%s) "
                 "interleaved_groups=%lld unaligned_groups=%lld span_groups=%lld "
-                "line_groups=%lld general_groups=%lld "
+                "span_loads=%d line_groups=%lld general_groups=%lld "
                 "lds_limit=%zu buckets=%zu radix_buckets=%d select=%s%s K_total=%lld "
                 "payload=%lld",
                 comp, c->tensor_mode ? "tensors" : "single_view", sketch, c->widths.size(),
@@ -1094,6 +1096,7 @@ arc_status arc_describe(const arc_ctx* c, char* buf, int64_t len) {
                 occ[2].waves, occ[2].one_per_cu ? "/cu" : "", occ[3].waves,
                 occ[3].one_per_cu ? "/cu" : "", strided, unaligned,
                 static_cast<long long>(c->vec_count[arc::kSpanList]),
+                c->vec_count[arc::kSpanList] > 0 ? arc::span_loads(c->span_values) : 0,
                 static_cast<long long>(c->vec_count[arc::kLinesList]),
                 static_cast<long long>(ngroups - c->nvec_groups),
                 c->max_lds_per_block, c->buckets.size(),

@@ -74,7 +74,8 @@ struct arc_ctx {
   std::array<int64_t, arc::kVecLists> vec_count{};  // groups per vectorisable list
   std::array<int64_t, arc::kVecLists + 1> stage_elems{};  // coordinates per list, general last
   std::array<arc::SketchOccupancy, arc::kWindowLists> vec_occ{};  // launch shapes
-  int32_t span_floats = 0;  // LDS floats of a wave of the narrow rows' launch
+  // LDS floats and most values of a wave of the narrow rows' launch
+  int32_t span_floats = 0, span_values = 0;
   // per-tensor gather
   std::vector<arc::GatherBucket> gather;
   int64_t gather_work = 0;

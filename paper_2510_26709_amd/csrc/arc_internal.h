@@ -133,7 +133,8 @@ hipError_t launch_sketch_per_worker(int32_t group_rows, bool unaligned, const vo
 // Narrow rows (arc_span.hip): the same results for groups of up to 64
 // consecutive rows of at most kSpanValues values in all, any alignment, r in
 // {1, 2, 4, 8}.  norm (r = 1): squared row norms instead of sketches.
-// wave_floats: the largest span_wave_floats of the groups.
+// wave_floats and wave_values: the largest span_wave_floats and the most values
+// of the groups.
 constexpr int32_t kSpanValues = 4096;
 // LDS floats from one row to the next: whole float4s, an odd number of them,
 // so that lanes reading the same columns of consecutive rows hit distinct
@@ -144,10 +145,24 @@ __host__ __device__ constexpr int32_t span_pitch(int32_t n) { return (((n + 3) /
 constexpr int32_t span_wave_floats(int32_t rows, int32_t n, int32_t r) {
   return rows * span_pitch(n) + (n * r + 255) / 256 * 256 + 4;
 }
+// 16-byte loads per array and lane that take a span of `values` values, which
+// starts up to 31 values past a line: the kernel's forms.  A wave takes 64 rows
+// at most, so narrow rows give short spans, and loads past the span's end cost
+// their issue and the arithmetic on them although no memory moves (17 loads for
+// every span: rows of 4 values 883 us a step on 8.0e7 binary32 values, 4
+// workers, 8 values 509, 12 values 374; now 395, 303 and 285.  The window
+// kernels: 566, 338 and 276).
+constexpr int32_t kMaxSpanLoads = kSpanValues / 256 + 1;
+constexpr int32_t span_loads(int32_t values) {
+  for (const int32_t loads : {3, 5, 9})
+    if (values + 31 <= loads * 256) return loads;
+  return kMaxSpanLoads;
+}
 hipError_t launch_sketch_span(const void* grad, int32_t grad_bf16, float* h, const float* g,
                               const float* V, const RowGroup* groups, int64_t ngroups, float* S,
                               int64_t d, int64_t m, int32_t N, int32_t r, float eta, float a,
-                              bool norm, int32_t wave_floats, hipStream_t stream);
+                              bool norm, int32_t wave_floats, int32_t wave_values,
+                              hipStream_t stream);
 
 // Wide rows off the 128-byte lines (arc_lines.hip): the same results for
 // groups of at most kLineRows rows of any width up to 2^22, any alignment, r

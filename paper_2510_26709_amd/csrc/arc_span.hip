@@ -20,10 +20,6 @@ namespace arc {
 namespace {
 
 constexpr uint32_t kDropOffset = 0x80000000u;  // beyond every resource here
-// 16-byte loads per array and lane: a span of kSpanValues values that starts
-// up to 31 values past a line.
-constexpr int kSpanLoads = kSpanValues / (4 * kWave) + 1;
-
 // One wave per workgroup and (row group, worker), at the occupancy its LDS
 // allows (6 per compute unit for rows of 512 values at r = 4).  Bound by HBM:
 // a wave streams once and ends, so what hides its latency is other waves.
@@ -31,7 +27,8 @@ constexpr int kSpanLoads = kSpanValues / (4 * kWave) + 1;
 // workgroup's LDS is held until its last wave ends), reservations that leave
 // 3 to 5 waves per compute unit 0.5-12%, spans of half the size 3%.  Registers
 // stay under half a SIMD's (two waves): at 258 instead of 233 the rows of 333
-// values took 330 us instead of 303.
+// values took 330 us instead of 303.  Short spans hold fewer loads and run more
+// waves (LOADS, see span_loads).
 // Step times (us), 4 workers of 2.0e7 values (8 of 1.2e7 for ResNet-18), the
 // window kernels / this one: 512-wide rows 32 bytes further off a line from
 // worker to worker (ResNet-18) 322 / 301; binary32 rows of 333 values 370 /
@@ -39,8 +36,8 @@ constexpr int kSpanLoads = kSpanValues / (4 * kWave) + 1;
 // at an odd base 280 / 227, of 681 285 / 247.  Rows on the lines stay with
 // the window kernels (512: 284 / 295, 768: 261 / 338), and rows too wide for
 // five to fit a span go to the lines kernel (1001: 266 / 295 before that).
-template <int R, bool BF16, bool NORM>
-__global__ void __launch_bounds__(kWave, 2)
+template <int R, bool BF16, bool NORM, int LOADS>
+__global__ void __launch_bounds__(kWave, LOADS == kMaxSpanLoads ? 2 : 4)
 sketch_span_kernel(const void* __restrict__ grad, float* __restrict__ h,
                    const float* __restrict__ g, const float* __restrict__ V,
                    const RowGroup* __restrict__ groups, int64_t ngroups, float* __restrict__ S,
@@ -96,11 +93,11 @@ sketch_span_kernel(const void* __restrict__ grad, float* __restrict__ h,
   // them start in the same half of a bf16 word.
   const bool half = BF16 && ((head + x_odd) & 1u) != 0;
 
-  float4 xv[kSpanLoads], hv[kSpanLoads], gv[kSpanLoads];
+  float4 xv[LOADS], hv[LOADS], gv[LOADS];
   // Load u's quad starts at span position at0 + u * 4 * kWave.
   int at0 = lane * 4 - shift;
 #pragma unroll
-  for (int u = 0; u < kSpanLoads; ++u) {
+  for (int u = 0; u < LOADS; ++u) {
     const int at = at0 + u * 4 * kWave;
     const uint32_t o = (uint32_t)at * 4u;
     if constexpr (BF16) {
@@ -176,10 +173,10 @@ sketch_span_kernel(const void* __restrict__ grad, float* __restrict__ h,
   };
   if (head == 0 && n % 4 == 0) {  // no quad crosses a row's end
 #pragma unroll
-    for (int u = 0; u < kSpanLoads; ++u) consume(u, std::true_type{});
+    for (int u = 0; u < LOADS; ++u) consume(u, std::true_type{});
   } else {
 #pragma unroll
-    for (int u = 0; u < kSpanLoads; ++u) consume(u, std::false_type{});
+    for (int u = 0; u < LOADS; ++u) consume(u, std::false_type{});
   }
   if (head + tail > 0 && end_ok && lane < 8) {
     const float hn = fmaf(eta, end_x, a * end_h);
@@ -250,18 +247,28 @@ sketch_span_kernel(const void* __restrict__ grad, float* __restrict__ h,
   }
 }
 
-template <int R, bool BF16, bool NORM>
-void launch_span(const void* grad, float* h, const float* g, const float* V,
-                 const RowGroup* groups, int64_t ngroups, float* S, int64_t d, int64_t m,
-                 int32_t N, float eta, float a, int32_t wave_floats, hipStream_t stream) {
+template <int R, bool BF16, bool NORM, int LOADS>
+void launch_span_loads(const void* grad, float* h, const float* g, const float* V,
+                       const RowGroup* groups, int64_t ngroups, float* S, int64_t d, int64_t m,
+                       int32_t N, float eta, float a, int32_t wave_floats, hipStream_t stream) {
   // The grid is one-dimensional for multiples of 8 workers, as the window
   // kernels' is.
   const bool flat = N % 8 == 0 && ngroups * N <= INT32_MAX;
   const unsigned n = (unsigned)ngroups;
-  hipLaunchKernelGGL((sketch_span_kernel<R, BF16, NORM>),
+  hipLaunchKernelGGL((sketch_span_kernel<R, BF16, NORM, LOADS>),
                      flat ? dim3(n * (unsigned)N) : dim3(n, (unsigned)N), dim3(kWave),
                      (size_t)wave_floats * sizeof(float), stream, grad, h, g, V, groups, ngroups,
                      S, d, m, eta, a, flat ? 1 : 0, wave_floats);
+}
+
+template <int R, bool BF16, bool NORM, typename... Args>
+void launch_span(int32_t wave_values, Args... args) {
+  switch (span_loads(wave_values)) {
+    case 3: launch_span_loads<R, BF16, NORM, 3>(args...); break;
+    case 5: launch_span_loads<R, BF16, NORM, 5>(args...); break;
+    case 9: launch_span_loads<R, BF16, NORM, 9>(args...); break;
+    default: launch_span_loads<R, BF16, NORM, kMaxSpanLoads>(args...);
+  }
 }
 
 }  // namespace
@@ -269,15 +276,16 @@ void launch_span(const void* grad, float* h, const float* g, const float* V,
 hipError_t launch_sketch_span(const void* grad, int32_t grad_bf16, float* h, const float* g,
                               const float* V, const RowGroup* groups, int64_t ngroups, float* S,
                               int64_t d, int64_t m, int32_t N, int32_t r, float eta, float a,
-                              bool norm, int32_t wave_floats, hipStream_t stream) {
+                              bool norm, int32_t wave_floats, int32_t wave_values,
+                              hipStream_t stream) {
   if (ngroups <= 0) return hipSuccess;
-#define ARC_SPAN(RR, NN)                                                                       \
-  if (grad_bf16)                                                                               \
-    launch_span<RR, true, NN>(grad, h, g, V, groups, ngroups, S, d, m, N, eta, a, wave_floats, \
-                              stream);                                                         \
-  else                                                                                         \
-    launch_span<RR, false, NN>(grad, h, g, V, groups, ngroups, S, d, m, N, eta, a,             \
-                               wave_floats, stream)
+#define ARC_SPAN(RR, NN)                                                                      \
+  if (grad_bf16)                                                                              \
+    launch_span<RR, true, NN>(wave_values, grad, h, g, V, groups, ngroups, S, d, m, N, eta,   \
+                              a, wave_floats, stream);                                        \
+  else                                                                                        \
+    launch_span<RR, false, NN>(wave_values, grad, h, g, V, groups, ngroups, S, d, m, N, eta,  \
+                               a, wave_floats, stream)
   if (norm) {
     ARC_SPAN(1, true);
     return hipGetLastError();

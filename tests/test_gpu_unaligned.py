@@ -3,9 +3,12 @@ bases that are not multiples of 4 values, arrays offset by single elements,
 bf16 rows that start in the upper half of a word, every r of the vectorised
 kernels, the ragged tail row and Top-K's row norms, against the oracle, bit
 for bit."""
+import re
+
 import pytest
 import torch
 
+import paper_2510_26709_amd as arc
 from parity_util import log, run_case
 from test_gpu_compare import run_compare_case
 
@@ -36,6 +39,28 @@ def test_parity_odd_widths(n, dtype):
         log(f"[unaligned] n={n} {dtype} r={r} N={N} d={d} misalign={mis}")
         run_case(label=f"odd_{n}_{dtype}_{k}", d=d, N=N, n=n, r=r, K=rows // 7 + 1, steps=2,
                  grad_dtype=dtype, family=1 if dtype == "bf16" else 0, misalign=mis, check_S=True)
+
+
+# Widths on both sides of the span kernel's forms (3, 5, 9 and 17 loads a lane
+# take 737, 1249, 2273 and 4096 values, 64 rows a span): worker bases 31 to 28
+# values past a line, the whole quads then starting at any of the four words,
+# several full spans, a partial one and a ragged row.
+@pytest.mark.parametrize("n,loads", [(4, 3), (7, 3), (11, 3), (12, 5), (19, 5), (20, 9), (35, 9),
+                                     (36, 17), (63, 17)])
+def test_span_loads_follow_the_rows(n, loads):
+    base = n * 330 // 32 * 32
+    for k, (dtype, r, mis, res) in enumerate([("f32", 4, 0, 31), ("bf16", 4, 1, 31),
+                                              ("f32", 1, 2, 28), ("bf16", 8, 3, 31),
+                                              ("f32", 2, 0, 28), ("bf16", 4, 0, 28)]):
+        d = base + res
+        log(f"[unaligned] span n={n} {dtype} r={r} misalign={mis}")
+        run_case(label=f"span_{n}_{k}", d=d, N=4, n=n, r=r, K=20, steps=2, grad_dtype=dtype,
+                 family=1 if dtype == "bf16" else 0, misalign=mis, check_S=True)
+    comp = arc.Compressor(d=d, N=4, n=n, r=4, K=20, eta=0.1, seed=1)
+    try:
+        assert f"span_loads={loads} " in comp.describe(), comp.describe()
+    finally:
+        comp.close()
 
 
 # Wide rows in groups of every 4th row (2307, 5001 values) and of every 4th
@@ -77,9 +102,6 @@ def test_ragged_row_shares_the_launch_of_its_view():
     # Rows on the lines and off them, narrow and wide, on 16 bytes and not:
     # the tail row never adds a list of its own (each non-empty list is one
     # launch of the streaming stage).
-    import re
-
-    import paper_2510_26709_amd as arc
     for n, d in ((3904, 3904 * 50 + 36), (2048, 2048 * 50 + 32), (512, 512 * 90 + 40),
                  (333, 333 * 90 + 2), (1001, 1001 * 50 + 3), (4099, 4099 * 40 + 1)):
         comp = arc.Compressor(d=d, N=2, n=n, r=4, K=3, eta=0.1, seed=1)
