@@ -60,7 +60,6 @@ sketch_span_kernel(const void* __restrict__ grad, float* __restrict__ h,
   const int pitch = span_pitch(n);
   float* tile = reinterpret_cast<float*>(lds);
   float* vt = tile + rows * pitch;
-  const bool split = !NORM && rows * R <= kWave;
 
   // This width's V (n x R) straight to LDS, first of all, so that it is there
   // when the span's own loads have come.
@@ -186,65 +185,55 @@ sketch_span_kernel(const void* __restrict__ grad, float* __restrict__ h,
   wave_vmem_fence();  // V's loads to LDS
   wave_lds_fence();
 
-  // Chains: lane row + k * rows column k of one row, or lane row all R.
-  if (split) {
-    int row = lane, k = 0;
+  // Chains: lane row + q * rows runs row `row` against columns [q * KPL,
+  // (q + 1) * KPL) of V (or its squares, NORM).
+  auto chains = [&](auto per_lane) __attribute__((always_inline)) {
+    constexpr int KPL = decltype(per_lane)::value;
+    int row = lane, q = 0;
 #pragma unroll
-    for (int q = 1; q < R; ++q)
+    for (int u = 1; u < R / KPL; ++u)
       if (row >= rows) {
         row -= rows;
-        ++k;
+        ++q;
       }
     const bool live = row < rows;
     const float* my_row = tile + (live ? row : 0) * pitch;
-    const float* my_v = vt + k;
-    float s = 0.0f;
+    const float* my_v = vt + q * KPL;
+    float s[KPL];
+#pragma unroll
+    for (int k = 0; k < KPL; ++k) s[k] = 0.0f;
+    auto term = [&](float dv, int j) __attribute__((always_inline)) {
+#pragma unroll
+      for (int k = 0; k < KPL; ++k) s[k] = fmaf(dv, NORM ? dv : my_v[j * R + k], s[k]);
+    };
     int j = 0;
-#pragma unroll 8
+#pragma unroll(KPL == 1 && !NORM ? 8 : KPL == 2 && R > 2 ? 4 : 2)
     for (; j + 4 <= n; j += 4) {
       const float4 dv = *reinterpret_cast<const float4*>(my_row + j);
-      s = fmaf(dv.x, my_v[j * R], s);
-      s = fmaf(dv.y, my_v[(j + 1) * R], s);
-      s = fmaf(dv.z, my_v[(j + 2) * R], s);
-      s = fmaf(dv.w, my_v[(j + 3) * R], s);
+      term(dv.x, j);
+      term(dv.y, j + 1);
+      term(dv.z, j + 2);
+      term(dv.w, j + 3);
     }
-    for (; j < n; ++j) s = fmaf(my_row[j], my_v[j * R], s);
-    if (live) S[((int64_t)i * m + grp.row0 + row) * R + k] = s;
-  } else {
-    const float* my_row = tile + (lane < rows ? lane : 0) * pitch;
-    float s[R];
+    for (; j < n; ++j) term(my_row[j], j);
+    if (live) {
+      float* out = S + ((int64_t)i * m + grp.row0 + row) * R + q * KPL;
 #pragma unroll
-    for (int k = 0; k < R; ++k) s[k] = 0.0f;
-    int j = 0;
-#pragma unroll 2
-    for (; j + 4 <= n; j += 4) {
-      const float4 dv = *reinterpret_cast<const float4*>(my_row + j);
-      const float e4[4] = {dv.x, dv.y, dv.z, dv.w};
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        if constexpr (NORM) {
-          s[0] = fmaf(e4[jj], e4[jj], s[0]);
-        } else {
-#pragma unroll
-          for (int k = 0; k < R; ++k) s[k] = fmaf(e4[jj], vt[(j + jj) * R + k], s[k]);
-        }
-      }
+      for (int k = 0; k < KPL; ++k) out[k] = s[k];
     }
-    for (; j < n; ++j) {
-      const float dv = my_row[j];
-      if constexpr (NORM) {
-        s[0] = fmaf(dv, dv, s[0]);
-      } else {
-#pragma unroll
-        for (int k = 0; k < R; ++k) s[k] = fmaf(dv, vt[j * R + k], s[k]);
-      }
-    }
-    if (lane < rows) {
-      float* out = S + ((int64_t)i * m + grp.row0 + lane) * R;
-#pragma unroll
-      for (int k = 0; k < R; ++k) out[k] = s[k];
-    }
-  }
+  };
+  // As few columns a lane as the rows leave lanes for: with all eight chains of
+  // nine rows on nine lanes, rows of 416 values took 362 us a step (r = 8,
+  // 8.0e7 binary32 values; the window kernel 289), with two a lane 280.  Short
+  // spans have all 64 rows.
+  if (!NORM && rows * R <= kWave)
+    chains(std::integral_constant<int, 1>{});
+  else if (LOADS == kMaxSpanLoads && R >= 4 && rows * (R / 2) <= kWave)
+    chains(std::integral_constant<int, R >= 4 ? 2 : R>{});
+  else if (LOADS == kMaxSpanLoads && R >= 8 && rows * (R / 4) <= kWave)
+    chains(std::integral_constant<int, R >= 8 ? 4 : R>{});
+  else
+    chains(std::integral_constant<int, R>{});
 }
 
 template <int R, bool BF16, bool NORM, int LOADS>

@@ -63,6 +63,16 @@ def test_span_loads_follow_the_rows(n, loads):
         comp.close()
 
 
+# Spans of 8 to 32 rows, around the counts where a lane takes one, two, four or
+# all of a row's chains (rows * r / chains <= 64), and their partial last spans.
+@pytest.mark.parametrize("n", [127, 128, 129, 131, 204, 240, 241, 255, 315, 400, 455, 456, 512])
+def test_span_chains_per_lane(n):
+    for r, dtype in ((8, "f32"), (4, "bf16"), (8, "bf16"), (2, "f32")):
+        log(f"[unaligned] chains n={n} r={r} {dtype}")
+        run_case(label=f"chains_{n}_{r}", d=n * 77 + 11, N=2, n=n, r=r, K=9, steps=2,
+                 grad_dtype=dtype, family=1 if dtype == "bf16" else 0, check_S=True)
+
+
 # Wide rows in groups of every 4th row (2307, 5001 values) and of every 4th
 # and 2nd at power-of-two widths, with a ragged tail row.
 @pytest.mark.parametrize("n,dtype,mis", [(2307, "f32", 1), (2307, "bf16", 0), (5001, "bf16", 3),
