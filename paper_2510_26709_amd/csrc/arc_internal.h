@@ -151,10 +151,11 @@ constexpr int32_t span_wave_floats(int32_t rows, int32_t n, int32_t r) {
 // their issue and the arithmetic on them although no memory moves (17 loads for
 // every span: rows of 4 values 883 us a step on 8.0e7 binary32 values, 4
 // workers, 8 values 509, 12 values 374; now 395, 303 and 285.  The window
-// kernels: 566, 338 and 276).
+// kernels: 566, 338 and 276).  From 28 values a row on the longest form is as
+// fast or faster (nine loads for 33 values: 293 us, one worker; now 284).
 constexpr int32_t kMaxSpanLoads = kSpanValues / 256 + 1;
 constexpr int32_t span_loads(int32_t values) {
-  for (const int32_t loads : {3, 5, 9})
+  for (const int32_t loads : {3, 5, 7})
     if (values + 31 <= loads * 256) return loads;
   return kMaxSpanLoads;
 }

@@ -255,7 +255,7 @@ void launch_span(int32_t wave_values, Args... args) {
   switch (span_loads(wave_values)) {
     case 3: launch_span_loads<R, BF16, NORM, 3>(args...); break;
     case 5: launch_span_loads<R, BF16, NORM, 5>(args...); break;
-    case 9: launch_span_loads<R, BF16, NORM, 9>(args...); break;
+    case 7: launch_span_loads<R, BF16, NORM, 7>(args...); break;
     default: launch_span_loads<R, BF16, NORM, kMaxSpanLoads>(args...);
   }
 }
