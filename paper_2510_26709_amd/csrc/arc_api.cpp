@@ -283,26 +283,56 @@ int32_t row_interleave(int64_t cols, int32_t group_rows) {
 // arc_sketch.hip (column windows), arc_span.hip and arc_lines.hip.
 enum class RowKernel { kGeneral, kWindow, kSpan, kLines };
 
+// Rows of one span.
+int64_t span_rows(int64_t rows, int64_t cols) {
+  return std::min<int64_t>({kGroupRows, std::max<int64_t>(1, arc::kSpanValues / cols), rows});
+}
+
 // Rows off the 128-byte lines (a width or a worker base that is not a multiple
-// of 32 values): spans where at least five rows fit in one, else the lines
-// kernel.  Step us on 2.0e7 values, 4 workers, span / window kernels on the
-// rows as they lie: 800 values 269 / 531, 801 311 / 324, 1001 378 / 312 (four
-// rows a span); the lines kernel takes 281 at 1001.  A span row shorter than
-// four values can end twice within one 16-byte access, so only a lone row may
-// be.
+// of 32 values): spans where at least five rows fit in one and either six
+// waves' LDS fit a compute unit or all waves run at once (four a compute unit),
+// else the lines kernel.  V's n * r floats share a wave's
+// LDS, so r = 8 reaches the second bound at about 330 values, r = 4 at 650 (683
+// to 720, five rows a span, lie inside again), r = 2 and Top-K's norms never.  Step us, 4 workers whose bases lie 32 bytes apart
+// from a line, binary32, span / lines: 768 values, r = 4 (five waves a compute
+// unit), 6e6 values in all 48 / 40, 1.2e7 68 / 59, 2.4e7 104 / 98, 8e7 272 /
+// 276; bf16 227 / 224 at 8e7; 817 values 314 / 276; 720 (six waves) 267 / 278;
+// 800 values, r = 8 (three) 326 / 282, bf16 303 / 232; 500 (four) 284 / 295,
+// bf16 242 / 249, 501 329 / 286.  The stage alone, 768 values: 768 waves of
+// spans 17.0 / 19.0, 1042 waves 20.8 / 20.3, 1563 32.0 / 22.5.  Five rows of 801 values against four of 1001:
+// span 311, 378, lines 324, 281.  A span row shorter than four values can end
+// twice within one 16-byte access, so only a lone row may be.
 constexpr int64_t kSpanMaxCols = arc::kSpanValues / 5;
 constexpr int64_t kSpanMinCols = 4;
-RowKernel off_line_kernel(int64_t rows, int64_t cols) {
-  if (cols <= kSpanMaxCols)
-    return cols >= kSpanMinCols || rows == 1 ? RowKernel::kSpan : RowKernel::kWindow;
-  return RowKernel::kLines;
+constexpr int64_t kSpanWavesAtOnce = 4 * 256;
+RowKernel off_line_kernel(int64_t rows, int64_t cols, int32_t r, int32_t N) {
+  if (cols > kSpanMaxCols) return RowKernel::kLines;
+  if (cols < kSpanMinCols && rows != 1) return RowKernel::kWindow;
+  const auto n = static_cast<int32_t>(cols);
+  const auto span = static_cast<int32_t>(span_rows(std::max<int64_t>(rows, 1), cols));
+  const bool six = arc::span_wave_floats(span, n, r) <= arc::kSpanMaxFloats;
+  const bool at_once = (rows + span - 1) / span * N <= kSpanWavesAtOnce;
+  return six || at_once ? RowKernel::kSpan : RowKernel::kLines;
+}
+
+// Whether the rows of one m x n view keep the window kernels.  On the lines
+// (n and every worker's base multiples of 32 values) they do.  So do rows that
+// lie on 16 bytes and all start the same distance past a line where the
+// windows' common shift does as well: wide ones (2048 values at a base 32 bytes
+// past a line: window 252, lines kernel 271 us), and one worker's, whose base
+// is on a line whatever d is, at whole chunks of 256 columns (8.0e7 values,
+// d = 4 mod 32, window / span or lines: 256 values 266 / 268, 512 258 / 270,
+// 768 270 / 275; at other multiples of 32 the spans are faster: 320 278 / 268,
+// 608 309 / 272, 800 318 / 279).
+bool window_view(int64_t d, int64_t n, int32_t N, bool aligned) {
+  if (n % 32 != 0) return false;
+  return d % 32 == 0 || (aligned && (n > kSpanMaxCols || (N == 1 && n % 256 == 0)));
 }
 
 // Groups of the span kernel: as many consecutive rows as fit, up to 64.
 void add_span_groups(int64_t elem_off, int64_t row0, int64_t rows, int64_t cols, int64_t v_off,
                      GroupLists* out) {
-  const int64_t step =
-      std::min<int64_t>(kGroupRows, std::max<int64_t>(1, arc::kSpanValues / cols));
+  const int64_t step = span_rows(std::max<int64_t>(rows, 1), cols);
   for (int64_t p = 0; p < rows; p += step) {
     arc::RowGroup grp{};
     grp.elem_off = elem_off + p * cols;
@@ -382,6 +412,7 @@ void build_plan(const arc_config* cfg, arc::PlanKind kind, arc_ctx* c) {
   std::vector<int64_t> begin{0}, want;
   // r in {1,2,4,8} for the vectorised sketch; the other compressors use no V.
   const bool r_ok = c->compressor != ARC_COMP_ARC || vector_r(c->r);
+  const int32_t span_r = c->compressor == ARC_COMP_ARC ? c->r : 0;  // columns of V in LDS
   // Row groups' size for the vectorised kernels under this kind of plan.
   const auto group_rows = [&](bool aligned, int64_t cols) {
     if (!r_ok || kind == arc::PlanKind::kGeneral ||
@@ -406,12 +437,10 @@ void build_plan(const arc_config* cfg, arc::PlanKind kind, arc_ctx* c) {
     if (gr > 0) {
       // The ragged row is a one-row group as wide as its values, in the same
       // launch as the others.
-      // Rows on 16 bytes that all start the same distance past a line keep
-      // the window kernels' common shift where they are wide.
-      const bool on_lines = c->n % 32 == 0 && (c->d % 32 == 0 || (aligned && c->n > kSpanMaxCols));
-      const RowKernel kernel = on_lines || kind != arc::PlanKind::kFast
-                                   ? RowKernel::kWindow
-                                   : off_line_kernel(m_full, c->n);
+      const RowKernel kernel =
+          kind != arc::PlanKind::kFast || window_view(c->d, c->n, c->N, aligned)
+              ? RowKernel::kWindow
+              : off_line_kernel(m_full, c->n, span_r, c->N);
       const int64_t tail = c->d - m_full * c->n;
       add_groups(0, 0, m_full, c->n, c->n, 0, kernel, gr, aligned, &lists);
       if (tail > 0)
@@ -467,7 +496,7 @@ void build_plan(const arc_config* cfg, arc::PlanKind kind, arc_ctx* c) {
       const int32_t gr = group_rows(aligned, t.cols);
       const RowKernel kernel = gr == 0   ? RowKernel::kGeneral
                                : aligned ? RowKernel::kWindow
-                                         : off_line_kernel(t.rows, t.cols);
+                                         : off_line_kernel(t.rows, t.cols, span_r, c->N);
       add_groups(off, row0, t.rows, t.cols, t.cols, c->v_off[t.cols], kernel, gr, aligned,
                  &lists);
       off += t.rows * t.cols;
@@ -510,9 +539,8 @@ void build_plan(const arc_config* cfg, arc::PlanKind kind, arc_ctx* c) {
   }
   c->nvec_groups = static_cast<int64_t>(c->groups.size());
   for (const arc::RowGroup& grp : lists.vec[arc::kSpanList]) {
-    c->span_floats = std::max(
-        c->span_floats, arc::span_wave_floats(grp.rows, grp.cols,
-                                              c->compressor == ARC_COMP_ARC ? c->r : 0));
+    c->span_floats =
+        std::max(c->span_floats, arc::span_wave_floats(grp.rows, grp.cols, span_r));
     c->span_values = std::max(c->span_values, grp.rows * grp.cols);
   }
   c->groups.insert(c->groups.end(), lists.general.begin(), lists.general.end());

@@ -145,6 +145,9 @@ __host__ __device__ constexpr int32_t span_pitch(int32_t n) { return (((n + 3) /
 constexpr int32_t span_wave_floats(int32_t rows, int32_t n, int32_t r) {
   return rows * span_pitch(n) + (n * r + 255) / 256 * 256 + 4;
 }
+// The most of it that lets six waves (one a workgroup) share a compute unit,
+// whose 160 KB are given out in pieces of 1280 bytes.
+constexpr int32_t kSpanMaxFloats = 160 * 1024 / 6 / 1280 * 1280 / 4;
 // 16-byte loads per array and lane that take a span of `values` values, which
 // starts up to 31 values past a line: the kernel's forms.  A wave takes 64 rows
 // at most, so narrow rows give short spans, and loads past the span's end cost

@@ -108,6 +108,39 @@ def test_topk_norms_unaligned(n, dtype, mis):
                      family=1 if dtype == "bf16" else 0, misalign=mis, label=f"topk_{n}_{dtype}")
 
 
+def _kernel_of(desc):
+    """The one list of row groups of a single view."""
+    windows = re.search(r"\(64:(\d+) 32:(\d+) 16:(\d+) 8:(\d+) rows\)", desc).groups()
+    count = {key: int(re.search(key + r"_groups=(\d+)", desc).group(1))
+             for key in ("span", "line", "general")}
+    count["window"] = sum(int(c) > 0 for c in windows)
+    used = [key for key, c in count.items() if c > 0]
+    assert len(used) == 1 and count["window"] <= 1, desc
+    return used[0]
+
+
+# One worker's rows of whole 256-column chunks are on the lines whatever d is;
+# several workers' are not.  Spans where six waves' LDS fits a compute unit or
+# few waves are needed; the rows of a view are counted, its tail is not.
+@pytest.mark.parametrize("n,rows,N,res,r,want", [
+    (256, 60, 1, 4, 4, "window"), (512, 60, 1, 8, 4, "window"), (768, 6000, 1, 4, 8, "window"),
+    (768, 60, 1, 0, 4, "window"), (768, 60, 4, 0, 4, "window"), (512, 60, 1, 1, 4, "span"),
+    (320, 60, 1, 4, 4, "span"), (512, 60, 4, 4, 4, "span"), (2048, 60, 2, 4, 4, "window"),
+    (768, 1270, 4, 4, 4, "span"), (768, 1290, 4, 4, 4, "line"), (768, 2580, 2, 4, 2, "span"),
+    (640, 2000, 4, 4, 4, "span"), (704, 1400, 4, 8, 4, "span"), (800, 5200, 1, 4, 4, "line"),
+    (320, 4000, 4, 4, 8, "span"), (512, 2070, 4, 4, 8, "line"), (819, 2570, 2, 1, 4, "line"),
+    (819, 2570, 2, 1, 1, "span")])
+def test_kernel_of_the_rows(n, rows, N, res, r, want):
+    d = n * rows // 32 * 32 + res
+    comp = arc.Compressor(d=d, N=N, n=n, r=r, K=3, eta=0.1, seed=1)
+    try:
+        assert _kernel_of(comp.describe()) == want, comp.describe()
+    finally:
+        comp.close()
+    log(f"[unaligned] route n={n} rows={rows} N={N} res={res} r={r}")
+    run_case(label=f"route_{n}_{N}_{res}_{r}", d=d, N=N, n=n, r=r, K=7, steps=1, check_S=True)
+
+
 def test_ragged_row_shares_the_launch_of_its_view():
     # Rows on the lines and off them, narrow and wide, on 16 bytes and not:
     # the tail row never adds a list of its own (each non-empty list is one
@@ -119,7 +152,4 @@ def test_ragged_row_shares_the_launch_of_its_view():
             desc = comp.describe()
         finally:
             comp.close()
-        windows = re.search(r"\(64:(\d+) 32:(\d+) 16:(\d+) 8:(\d+) rows\)", desc).groups()
-        others = [re.search(key + r"_groups=(\d+)", desc).group(1)
-                  for key in ("span", "line", "general")]
-        assert sum(int(c) > 0 for c in list(windows) + others) == 1, (n, d, desc)
+        _kernel_of(desc)
