@@ -17,9 +17,11 @@ def _gpu():
         pytest.skip("no GPU")
 
 
-@pytest.mark.parametrize("N", [1, 3, 4, 5, 9])
+# Four workers at a time up to 8, then eight; rows as single columns and, from
+# 12 (one worker) or 128 values on, as quads and single columns.
+@pytest.mark.parametrize("N", [1, 3, 4, 5, 8, 9, 16, 17])
 def test_gather_worker_batches_and_remainders(N):
-    for n in (5, 6, 7, 8):
+    for n in (1, 3, 4, 5, 6, 7, 8, 11, 13, 31, 127, 129, 130, 131):
         log(f"[gather] N={N} n={n}")
         run_case(label=f"gather_{N}_{n}", d=n * 90 + n // 2, N=N, n=n, K=31, steps=2)
     tensors = [(20, 5, 3), (9, 6, 9), (31, 7, 8), (12, 8, 5), (1, 3, 1), (40, 65, 11)]
