@@ -548,6 +548,14 @@ void build_plan(const arc_config* cfg, arc::PlanKind kind, arc_ctx* c) {
     c->stage_elems[arc::kVecLists] += (grp.rows - 1) * static_cast<int64_t>(grp.cols) + grp.last_len;
 }
 
+// Values of the smaller streaming launches, over all workers, from which on they
+// run beside the largest on a second stream instead of before it.  The fork and
+// join cost up to 37 us where the launches are short (step us, forked / in
+// turn: 100 rows of 33 values and a row of 100 62 / 23; GPT-2 layouts of hidden
+// size 64 to 256, 2.8e5 to 1.9e7 values in all 57 / 27 to 118 / 115; CIFAR
+// ResNet-18, 4 workers, 4.5e7 values 273 / 270, 8 workers 493 / 499).
+constexpr int64_t kForkElems = 30'000'000;
+
 template <typename T>
 arc_status dev_alloc(T** p, size_t count, const char* what) {
   if (count == 0) count = 1;
@@ -725,9 +733,12 @@ arc_status arc_create(const arc_config* cfg, void* hip_stream, arc_ctx** out) {
     }
   }
   {
-    int launches = c->stage_elems[arc::kVecLists] > 0 ? 1 : 0;
-    for (int sz = 0; sz < arc::kVecLists; ++sz) launches += c->vec_count[sz] > 0;
-    if (launches > 1) {
+    int64_t all = 0, big = 0;
+    for (const int64_t elems : c->stage_elems) {
+      all += elems;
+      big = std::max(big, elems);
+    }
+    if ((all - big) * c->N >= kForkElems) {
       e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking);
       for (int k = 0; k < arc::kProjectionSlots && e == hipSuccess; ++k) {
         e = hipEventCreateWithFlags(&c->fork_ev[k], hipEventDisableTiming);
@@ -808,9 +819,9 @@ arc_status check_step_args(const arc_ctx* c, int64_t t, const void* grad, const 
 namespace {
 
 // The streaming stage (S1-S3; norm: Top-K's row norms): one launch per
-// non-empty list of row groups.  When there are several, the one over the
-// most coordinates runs on the caller's stream and the others on the second
-// stream, forked after everything queued before and joined before anything
+// non-empty list of row groups, in turn on the caller's stream, or, where the
+// context holds a second stream (kForkElems), the one over the most coordinates
+// on the caller's stream and the others on the second one, forked after everything queued before and joined before anything
 // queued after, so that they overlap it instead of following it.  Without
 // `aligned` (grad, h and g on 16 bytes) the lists of aligned rows take the
 // unaligned kernels too.
@@ -1115,7 +1126,7 @@ arc_status arc_describe(const arc_ctx* c, char* buf, int64_t len) {
                 "(64:%lld 32:%lld 16:%lld 8:%lld rows) workgroup_waves=(%d%s %d%s %d%s %d%s) "
                 "interleaved_groups=%lld unaligned_groups=%lld span_groups=%lld "
                 "span_loads=%d line_groups=%lld general_groups=%lld "
-                "lds_limit=%zu buckets=%zu radix_buckets=%d select=%s%s K_total=%lld "
+                "forked=%d lds_limit=%zu buckets=%zu radix_buckets=%d select=%s%s K_total=%lld "
                 "payload=%lld",
                 comp, c->tensor_mode ? "tensors" : "single_view", sketch, c->widths.size(),
                 static_cast<long long>(ngroups), static_cast<long long>(c->nvec_groups),
@@ -1126,7 +1137,7 @@ arc_status arc_describe(const arc_ctx* c, char* buf, int64_t len) {
                 static_cast<long long>(c->vec_count[arc::kSpanList]),
                 c->vec_count[arc::kSpanList] > 0 ? arc::span_loads(c->span_values) : 0,
                 static_cast<long long>(c->vec_count[arc::kLinesList]),
-                static_cast<long long>(ngroups - c->nvec_groups),
+                static_cast<long long>(ngroups - c->nvec_groups), c->side != nullptr,
                 c->max_lds_per_block, c->buckets.size(),
                 radix, c->select_ws().small ? "one_workgroup_per_bucket" : "blocks:",
                 c->select_ws().small ? "" : std::to_string(c->blocks.size()).c_str(),

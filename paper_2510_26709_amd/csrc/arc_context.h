@@ -82,7 +82,7 @@ struct arc_ctx {
   // device
   hipStream_t stream = nullptr;
   // second stream for the smaller launches of the streaming stage, forked
-  // from and joined back into `stream` (only when there are several)
+  // from and joined back into `stream` (only where they are long enough)
   hipStream_t side = nullptr;
   // a pair of events per step in flight, used in turn (an event is
   // re-recorded only after kProjectionSlots further steps)
