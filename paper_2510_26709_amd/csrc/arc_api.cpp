@@ -1074,8 +1074,8 @@ arc_status arc_model_step(arc_ctx* c, const arc_model_config* mc, int64_t t, con
   o.weight_decay = mc->weight_decay;
   o.fN = static_cast<float>(c->N);
   const bool cap = c->lds_per_cu == arc::kLdsPerCu;
-  const bool aligned = c->d % 4 == 0 && aligned16(G) && aligned16(x) &&
-                       (o.kind < 1 || aligned16(opt_m)) && (o.kind < 2 || aligned16(opt_v));
+  const bool aligned = aligned16(G) && aligned16(x) && (o.kind < 1 || aligned16(opt_m)) &&
+                       (o.kind < 2 || aligned16(opt_v));
   if (dense) {
     // Where the workers' arrays lie on 16 bytes, one pass; else the x update
     // reads G again (one pass at word alignment: 3 bf16 workers of 6.0e7 values
@@ -1094,7 +1094,11 @@ arc_status arc_model_step(arc_ctx* c, const arc_model_config* mc, int64_t t, con
     st = arc::enqueue_step(c, t, grad, h, g, out_idx, out_agg, G);
     if (st != ARC_OK) return st;
   }
-  ARC_HIP(arc::launch_optimizer(aligned, cap, o, G, x, opt_m, opt_v, c->d, c->stream),
+  // grad, h and g of every worker, G, x and the optimiser's state.
+  const double bytes = static_cast<double>(c->d) *
+                       (static_cast<double>(c->N) * (c->grad_bf16 ? 10 : 12) + 8 + 4 * o.kind);
+  const bool cached = bytes <= static_cast<double>(arc::kInfinityCacheBytes);
+  ARC_HIP(arc::launch_optimizer(aligned, cached, cap, o, G, x, opt_m, opt_v, c->d, c->stream),
           "optimizer launch");
   return ARC_OK;
 }

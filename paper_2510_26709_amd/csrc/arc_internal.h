@@ -278,10 +278,13 @@ hipError_t launch_dense_model(bool aligned, bool cap, const OptimizerArgs& o, co
                               hipStream_t stream);
 
 // x (and m, v) updated from G over every coordinate, at any element alignment.
-// aligned: 16-byte aligned arrays and d % 4 == 0; cap: the device has the
-// MI355X's 160 KB of LDS per compute unit, used to cap the launch's occupancy.
-hipError_t launch_optimizer(bool aligned, bool cap, const OptimizerArgs& o, const float* G, float* x, float* m,
-                            float* v, int64_t d, hipStream_t stream);
+// aligned: 16-byte aligned arrays; cached: the step's arrays fit the Infinity
+// Cache; cap: the device has the MI355X's 160 KB of LDS per compute
+// unit, used to cap the launch's occupancy.
+constexpr int64_t kInfinityCacheBytes = 256 * 1024 * 1024;
+hipError_t launch_optimizer(bool aligned, bool cached, bool cap, const OptimizerArgs& o,
+                            const float* G, float* x, float* m, float* v, int64_t d,
+                            hipStream_t stream);
 
 // ---- host projection (arc_projection.cpp) ----
 // V_t (n x r, row-major) for the shared seed and step t.

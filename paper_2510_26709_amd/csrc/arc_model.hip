@@ -176,9 +176,10 @@ dense_step_scalar_kernel(const void* __restrict__ grad, int32_t grad_bf16,
 // thread in flight together), through buffer resources that end with
 // d's last whole quad: the hardware returns zero for loads past the end and
 // drops those stores, so the last, partial tile needs no branch; the last
-// d % 4 coordinates go one a thread.  Arrays need whole words only.  Loads are non-temporal (every value is
+// d % 4 coordinates go one a thread.  Loads are non-temporal (every value is
 // read once), stores non-temporal at device scope (read again only by later
-// launches).  Adam over 1.1e9 coordinates (28 bytes each), three MI355X
+// launches).  5.0e7 + 1 coordinates, against one a thread: SGD 245 -> 203 us a
+// step, heavy ball 289 -> 271.  Adam over 1.1e9 coordinates (28 bytes each), three MI355X
 // boxes, every variant in one process per box: one float4 per thread
 // through plain pointers 5.66 / 4.91-4.93 / 5.37-5.39 ms; this tile (four
 // float4 per thread, at most four workgroups per compute unit through the
@@ -234,21 +235,28 @@ optimizer_vec_kernel(OptimizerArgs o, const float* __restrict__ G, float* __rest
   }
 }
 
-// Adam where an array is off 16 bytes or d % 4 != 0, one coordinate a thread:
-// the tiles above take as long at 5.0e7 coordinates (bf16 step 417 / 418 us)
-// and 0.7 us longer at 3.0e5; SGD and heavy ball gain there (5.0e7
-// coordinates with SGD 307 -> 271 us a step, per-tensor CIFAR ResNet-18 with
-// heavy ball 260 -> 250).
+// One coordinate a thread, where an array is off 16 bytes (heavy ball, 2.0e7
+// coordinates, 4 workers 327 us a step, in tiles 342; SGD 24e6 120 / 124) or d %
+// 4 != 0.  Adam at such a d: the tiles above take as long at 5.0e7 coordinates
+// (bf16 step 417 / 418 us) and 0.7 us longer at 3.0e5.  SGD and heavy ball: steps
+// whose arrays fit the Infinity Cache, whose bandwidth the tiles' four
+// workgroups a compute unit do not reach.  Step us, one a thread / tiles, binary32, steps on the same arrays:
+// dense, one bf16 worker, 6.0e6 coordinates, heavy ball 46 / 54, SGD 39 / 46;
+// 1.1e7 80 / 95 and 70 / 82; 2.4e7 (beyond the cache) 214 / 208 and 196 / 178;
+// dense, 4 workers, 3.0e6 53 / 56, 6.0e6 (beyond) 116 / 106.
+template <int KIND>
 __global__ void __launch_bounds__(256)
-adam_scalar_kernel(OptimizerArgs o, const float* __restrict__ G, float* __restrict__ x,
-                   float* __restrict__ m, float* __restrict__ v, int64_t d) {
+optimizer_scalar_kernel(OptimizerArgs o, const float* __restrict__ G, float* __restrict__ x,
+                        float* __restrict__ m, float* __restrict__ v, int64_t d) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= d) return;
-  float xe = x[e], me = m[e], ve = v[e];
-  update_one<2>(o, G[e], xe, me, ve);
+  float xe = x[e], me = 0.0f, ve = 0.0f;
+  if constexpr (KIND >= 1) me = m[e];
+  if constexpr (KIND == 2) ve = v[e];
+  update_one<KIND>(o, G[e], xe, me, ve);
   x[e] = xe;
-  m[e] = me;
-  v[e] = ve;
+  if constexpr (KIND >= 1) m[e] = me;
+  if constexpr (KIND == 2) v[e] = ve;
 }
 
 // Dynamic LDS that caps the vectorised update at four workgroups per compute
@@ -299,24 +307,21 @@ hipError_t launch_dense_model(bool aligned, bool cap, const OptimizerArgs& o, co
   return hipGetLastError();
 }
 
-hipError_t launch_optimizer(bool aligned, bool cap, const OptimizerArgs& o, const float* G, float* x, float* m,
-                            float* v, int64_t d, hipStream_t stream) {
+hipError_t launch_optimizer(bool aligned, bool cached, bool cap, const OptimizerArgs& o,
+                            const float* G, float* x, float* m, float* v, int64_t d,
+                            hipStream_t stream) {
   if (d <= 0) return hipSuccess;
   if (d > INT64_MAX - kOptTile) return hipErrorInvalidValue;
-  const dim3 grid(blocks_for(d, kOptTile));
-  const size_t lds = cap ? kOptLdsCap : 0;
-#define ARC_OPT(KK)                                                                          \
-  hipLaunchKernelGGL(optimizer_vec_kernel<KK>, grid, dim3(256), lds, stream, o, G, x, m, v, d)
+  const bool tiles = aligned && (d % 4 == 0 || (!cached && o.kind != 2));
+  const dim3 grid(blocks_for(d, tiles ? kOptTile : 256));
+  const size_t lds = tiles && cap ? kOptLdsCap : 0;
+#define ARC_OPT(KK)                                                                     \
+  hipLaunchKernelGGL(tiles ? optimizer_vec_kernel<KK> : optimizer_scalar_kernel<KK>, grid, \
+                     dim3(256), lds, stream, o, G, x, m, v, d)
   switch (o.kind) {
     case 0: ARC_OPT(0); break;
     case 1: ARC_OPT(1); break;
-    case 2:
-      if (aligned)
-        ARC_OPT(2);
-      else
-        hipLaunchKernelGGL(adam_scalar_kernel, dim3(blocks_for(d, 256)), dim3(256), 0, stream, o,
-                           G, x, m, v, d);
-      break;
+    case 2: ARC_OPT(2); break;
     default: return hipErrorInvalidValue;
   }
 #undef ARC_OPT

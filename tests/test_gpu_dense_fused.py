@@ -43,6 +43,19 @@ def test_any_length_and_alignment(optimizer, dtype):
                        family=1 if dtype == "bf16" else 0, weight_decay=5e-4, misalign=mis)
 
 
+# The x update in tiles where d % 4 != 0, which steps take whose arrays exceed
+# the 256 MiB Infinity Cache (20 or 24 bytes a coordinate here; the sizes above
+# go one coordinate a thread): tails of 1 to 3 values beside a tile's end.
+@pytest.mark.parametrize("optimizer,rest,mis", [("sgd", 1, 0), ("sgd", 4095, 0), ("msgd", 3, 0),
+                                                ("msgd", 2, 0), ("msgd", 1, 3)])
+def test_x_update_beyond_the_cache(optimizer, rest, mis):
+    d = 3296 * 4096 + rest
+    assert 20 * d > 256 * 1024 * 1024
+    log(f"[dense] x update d={d} {optimizer} misalign={mis}")
+    run_model_case(label=f"beyond_{optimizer}_{rest}", d=d, N=1, n=4096, K=1, steps=2,
+                   dense_steps=1, optimizer=optimizer, weight_decay=5e-4, misalign=mis)
+
+
 # The workers' arrays on 16 bytes and the model's off them.
 @pytest.mark.parametrize("optimizer,dtype,mis", [("sgd", "f32", 1), ("msgd", "bf16", 2),
                                                  ("adam", "f32", 3), ("adam", "bf16", 1)])
