@@ -207,13 +207,22 @@ sketch_span_kernel(const void* __restrict__ grad, float* __restrict__ h,
       for (int k = 0; k < KPL; ++k) s[k] = fmaf(dv, NORM ? dv : my_v[j * R + k], s[k]);
     };
     int j = 0;
-#pragma unroll(KPL == 1 && !NORM ? 8 : KPL == 2 && R > 2 ? 4 : 2)
-    for (; j + 4 <= n; j += 4) {
-      const float4 dv = *reinterpret_cast<const float4*>(my_row + j);
-      term(dv.x, j);
-      term(dv.y, j + 1);
-      term(dv.z, j + 2);
-      term(dv.w, j + 3);
+    auto quad = [&](int at) __attribute__((always_inline)) {
+      const float4 dv = *reinterpret_cast<const float4*>(my_row + at);
+      term(dv.x, at);
+      term(dv.y, at + 1);
+      term(dv.z, at + 2);
+      term(dv.w, at + 3);
+    };
+    if constexpr (KPL == 1 && !NORM) {
+#pragma unroll 8
+      for (; j + 4 <= n; j += 4) quad(j);
+    } else if constexpr (KPL < R) {
+#pragma unroll 4
+      for (; j + 4 <= n; j += 4) quad(j);
+    } else {
+#pragma unroll 2
+      for (; j + 4 <= n; j += 4) quad(j);
     }
     for (; j < n; ++j) term(my_row[j], j);
     if (live) {
