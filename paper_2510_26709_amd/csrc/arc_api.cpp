@@ -1073,7 +1073,9 @@ arc_status arc_model_step(arc_ctx* c, const arc_model_config* mc, int64_t t, con
   o.eps = mc->eps;
   o.weight_decay = mc->weight_decay;
   o.fN = static_cast<float>(c->N);
-  const bool cap = c->lds_per_cu == arc::kLdsPerCu;
+  const auto cap = [&](int32_t bytes) {
+    return arc::may_reserve_lds(c->lds_per_cu, static_cast<int64_t>(c->max_lds_per_block), bytes);
+  };
   const bool aligned = aligned16(G) && aligned16(x) && (o.kind < 1 || aligned16(opt_m)) &&
                        (o.kind < 2 || aligned16(opt_v));
   if (dense) {
@@ -1082,8 +1084,8 @@ arc_status arc_model_step(arc_ctx* c, const arc_model_config* mc, int64_t t, con
     // with Adam as long as one value a lane in two passes, 8 binary32 workers
     // of 1.2e7 4% longer).
     if (c->d % 4 == 0 && aligned16(grad) && aligned16(h) && aligned16(g)) {
-      ARC_HIP(arc::launch_dense_model(aligned, cap, o, grad, c->grad_bf16, h, g, G, x, opt_m,
-                                      opt_v, c->d, c->N, c->eta, c->a, c->stream),
+      ARC_HIP(arc::launch_dense_model(aligned, cap(arc::kDenseLdsCap), o, grad, c->grad_bf16, h, g,
+                                      G, x, opt_m, opt_v, c->d, c->N, c->eta, c->a, c->stream),
               "dense model step launch");
       return ARC_OK;
     }
@@ -1098,7 +1100,8 @@ arc_status arc_model_step(arc_ctx* c, const arc_model_config* mc, int64_t t, con
   const double bytes = static_cast<double>(c->d) *
                        (static_cast<double>(c->N) * (c->grad_bf16 ? 10 : 12) + 8 + 4 * o.kind);
   const bool cached = bytes <= static_cast<double>(arc::kInfinityCacheBytes);
-  ARC_HIP(arc::launch_optimizer(aligned, cached, cap, o, G, x, opt_m, opt_v, c->d, c->stream),
+  ARC_HIP(arc::launch_optimizer(aligned, cached, cap(arc::kOptLdsCap), o, G, x, opt_m, opt_v, c->d,
+                                c->stream),
           "optimizer launch");
   return ARC_OK;
 }
@@ -1261,7 +1264,7 @@ arc_status bind_device(arc_ctx* c) {
                                 c->device),
           "hipDeviceGetAttribute");
   c->lds_per_cu = lds_cu;
-  if (lds_cu != kLdsPerCu || lds_limit < kLdsPerCu / 2 + 1024)
+  if (!may_reserve_lds(lds_cu, lds_limit, kLdsPerCu / 2 + 1024))
     for (auto& o : c->vec_occ) o.one_per_cu = 0;
   return ARC_OK;
 }

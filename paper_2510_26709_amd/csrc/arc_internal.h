@@ -110,6 +110,13 @@ constexpr int32_t vector_chunk_cols(int32_t group_rows) { return 2048 / group_ro
 // LDS of one compute unit of the MI355X (gfx950).
 constexpr int32_t kLdsPerCu = 160 * 1024;
 
+// Whether a launch may reserve `bytes` of dynamic LDS a workgroup to cap how many
+// run per compute unit: the reservations assume the gfx950 figure, and a device
+// or runtime that gives a workgroup less would refuse the launch.
+constexpr bool may_reserve_lds(int64_t lds_per_cu, int64_t per_block, int64_t bytes) {
+  return lds_per_cu == kLdsPerCu && bytes <= per_block;
+}
+
 // Shape of one launch of the vectorised sketch kernels: workgroups of `waves`
 // waves (2 or 4, one row group per wave), and, with one_per_cu, a dynamic LDS
 // reservation that makes every workgroup hold more than half of a compute
@@ -270,8 +277,10 @@ hipError_t launch_dense_step(const void* grad, int32_t grad_bf16, float* h, floa
                              int64_t d, int32_t N, float eta, float a, hipStream_t stream);
 
 // The dense step and the x update after it in one pass: grad, h and g 16-byte
-// aligned and d % 4 == 0; aligned: G, x, m and v 16-byte aligned too; cap as for
-// launch_optimizer.
+// aligned and d % 4 == 0; aligned: G, x, m and v 16-byte aligned too; cap: the
+// launch may reserve kDenseLdsCap bytes of LDS a workgroup, which caps it at two
+// workgroups per compute unit.
+constexpr int32_t kDenseLdsCap = 80 * 1024;
 hipError_t launch_dense_model(bool aligned, bool cap, const OptimizerArgs& o, const void* grad,
                               int32_t grad_bf16, float* h, float* g, float* G, float* x, float* m,
                               float* v, int64_t d, int32_t N, float eta, float a,
@@ -279,8 +288,9 @@ hipError_t launch_dense_model(bool aligned, bool cap, const OptimizerArgs& o, co
 
 // x (and m, v) updated from G over every coordinate, at any element alignment.
 // aligned: 16-byte aligned arrays; cached: the step's arrays fit the Infinity
-// Cache; cap: the device has the MI355X's 160 KB of LDS per compute
-// unit, used to cap the launch's occupancy.
+// Cache; cap: the launch may reserve kOptLdsCap bytes of LDS a workgroup, which
+// caps it at four workgroups per compute unit.
+constexpr int32_t kOptLdsCap = 36 * 1024;
 constexpr int64_t kInfinityCacheBytes = 256 * 1024 * 1024;
 hipError_t launch_optimizer(bool aligned, bool cached, bool cap, const OptimizerArgs& o,
                             const float* G, float* x, float* m, float* v, int64_t d,

@@ -84,9 +84,6 @@ __device__ __forceinline__ float4 load_grad4(const void* grad, int64_t at) {
 }
 
 constexpr int kDenseWorkers = 4;
-// Dynamic LDS that caps the fused dense step at two workgroups per compute
-// unit (of the MI355X's 160 KB).
-constexpr size_t kDenseLdsCap = 80 * 1024;
 
 template <bool BF16, int KIND, bool W>
 __global__ void __launch_bounds__(256)
@@ -258,10 +255,6 @@ optimizer_scalar_kernel(OptimizerArgs o, const float* __restrict__ G, float* __r
   if constexpr (KIND >= 1) m[e] = me;
   if constexpr (KIND == 2) v[e] = ve;
 }
-
-// Dynamic LDS that caps the vectorised update at four workgroups per compute
-// unit (of the MI355X's 160 KB).
-constexpr size_t kOptLdsCap = 36 * 1024;
 
 }  // namespace
 
