@@ -212,6 +212,8 @@ void build_selection_plan(const std::vector<int64_t>& begin, const std::vector<i
 
 struct GroupLists {
   std::vector<arc::RowGroup> vec[arc::kVecLists], general;
+  bool count_only = false;  // the groups are counted and not kept
+  int64_t count = 0;
 };
 
 // List of vectorisable groups of that many rows: 16-byte aligned rows, or any.
@@ -333,6 +335,10 @@ bool window_view(int64_t d, int64_t n, int32_t N, bool aligned) {
 void add_span_groups(int64_t elem_off, int64_t row0, int64_t rows, int64_t cols, int64_t v_off,
                      GroupLists* out) {
   const int64_t step = span_rows(std::max<int64_t>(rows, 1), cols);
+  if (out->count_only) {
+    out->count += (rows + step - 1) / step;
+    return;
+  }
   for (int64_t p = 0; p < rows; p += step) {
     arc::RowGroup grp{};
     grp.elem_off = elem_off + p * cols;
@@ -379,6 +385,11 @@ void add_groups(int64_t elem_off, int64_t row0, int64_t rows, int64_t cols, int6
   };
   int64_t p = 0;
   const int32_t S = group_rows > 0 ? row_interleave(cols, group_rows) : 1;
+  if (out->count_only) {
+    const int64_t strided = S > 1 ? rows / (S * step) * S : 0;
+    out->count += strided + (rows - strided * step + step - 1) / step;
+    return;
+  }
   if (S > 1)
     for (; p + S * step <= rows; p += S * step)
       for (int32_t ph = 0; ph < S; ++ph) push(p + ph, step, S);
@@ -406,13 +417,16 @@ void build_node_selection(const std::vector<int64_t>& begin, const std::vector<i
   c->K_node = c->K_total / c->N;
 }
 
-// Lowers the configuration to the kernels' tables (host side only).
-void build_plan(const arc_config* cfg, arc::PlanKind kind, arc_ctx* c) {
-  GroupLists lists;
-  std::vector<int64_t> begin{0}, want;
+// Columns of V that a wave of spans holds in LDS.
+int32_t span_r(const arc_ctx* c) { return c->compressor == ARC_COMP_ARC ? c->r : 0; }
+
+// Row groups and projection offsets of a plan of that kind.
+void plan_rows(const arc_config* cfg, arc::PlanKind kind, arc_ctx* c, GroupLists* lists) {
+  c->widths.clear();
+  c->v_off.clear();
+  c->v_floats = 0;
   // r in {1,2,4,8} for the vectorised sketch; the other compressors use no V.
   const bool r_ok = c->compressor != ARC_COMP_ARC || vector_r(c->r);
-  const int32_t span_r = c->compressor == ARC_COMP_ARC ? c->r : 0;  // columns of V in LDS
   // Row groups' size for the vectorised kernels under this kind of plan.
   const auto group_rows = [&](bool aligned, int64_t cols) {
     if (!r_ok || kind == arc::PlanKind::kGeneral ||
@@ -434,21 +448,52 @@ void build_plan(const arc_config* cfg, arc::PlanKind kind, arc_ctx* c) {
     const int64_t m_full = c->d / c->n;
     const bool aligned = c->d % 4 == 0 && c->n % 4 == 0;
     const int32_t gr = group_rows(aligned, c->n);
-    if (gr > 0) {
-      // The ragged row is a one-row group as wide as its values, in the same
-      // launch as the others.
-      const RowKernel kernel =
-          kind != arc::PlanKind::kFast || window_view(c->d, c->n, c->N, aligned)
-              ? RowKernel::kWindow
-              : off_line_kernel(m_full, c->n, span_r, c->N);
-      const int64_t tail = c->d - m_full * c->n;
-      add_groups(0, 0, m_full, c->n, c->n, 0, kernel, gr, aligned, &lists);
-      if (tail > 0)
-        add_groups(m_full * c->n, m_full, 1, tail, tail, 0, kernel, gr, aligned, &lists);
-    } else {
+    if (gr == 0) {
       add_groups(0, 0, c->m, c->n, c->d - (c->m - 1) * c->n, 0, RowKernel::kGeneral, 0, false,
-                 &lists);
+                 lists);
+      return;
     }
+    // The ragged row is a one-row group as wide as its values, in the same
+    // launch as the others.
+    const RowKernel kernel =
+        kind != arc::PlanKind::kFast || window_view(c->d, c->n, c->N, aligned)
+            ? RowKernel::kWindow
+            : off_line_kernel(m_full, c->n, span_r(c), c->N);
+    const int64_t tail = c->d - m_full * c->n;
+    add_groups(0, 0, m_full, c->n, c->n, 0, kernel, gr, aligned, lists);
+    if (tail > 0)
+      add_groups(m_full * c->n, m_full, 1, tail, tail, 0, kernel, gr, aligned, lists);
+    return;
+  }
+  // One view per tensor; tensors of equal width share one V_t.
+  for (int32_t b = 0; b < cfg->num_tensors; ++b) {
+    const int64_t w = cfg->tensors[b].cols;
+    if (c->v_off.emplace(w, c->v_floats).second) {
+      c->widths.push_back(w);
+      c->v_floats += padded(w * c->r);
+    }
+  }
+  int64_t off = 0, row0 = 0;
+  for (int32_t b = 0; b < cfg->num_tensors; ++b) {
+    const arc_tensor& t = cfg->tensors[b];
+    const bool aligned = c->d % 4 == 0 && off % 4 == 0 && t.cols % 4 == 0;
+    // Tensors on 16 bytes keep the window kernels, whose launches they share
+    // (per-tensor ResNet-18 377 us, 382 with its rows off the lines in the span
+    // and lines kernels).
+    const int32_t gr = group_rows(aligned, t.cols);
+    const RowKernel kernel = gr == 0   ? RowKernel::kGeneral
+                             : aligned ? RowKernel::kWindow
+                                       : off_line_kernel(t.rows, t.cols, span_r(c), c->N);
+    add_groups(off, row0, t.rows, t.cols, t.cols, c->v_off[t.cols], kernel, gr, aligned, lists);
+    off += t.rows * t.cols;
+    row0 += t.rows;
+  }
+}
+
+// Lowers the configuration to the kernels' tables (host side only).
+void build_plan(const arc_config* cfg, const arc::PlanFits& fits, arc_ctx* c) {
+  std::vector<int64_t> begin{0}, want;
+  if (!c->tensor_mode) {
     if (cfg->num_buckets == 0) {
       begin.push_back(c->m);
       want.push_back(cfg->K);
@@ -478,35 +523,14 @@ void build_plan(const arc_config* cfg, arc::PlanKind kind, arc_ctx* c) {
     }
     c->gather_work = c->compressor == ARC_COMP_TOPK ? work : 0;
   } else {
-    // One view per tensor; tensors of equal width share one V_t.
+    int64_t row0 = 0;
     for (int32_t b = 0; b < cfg->num_tensors; ++b) {
-      const int64_t w = cfg->tensors[b].cols;
-      if (c->v_off.emplace(w, c->v_floats).second) {
-        c->widths.push_back(w);
-        c->v_floats += padded(w * c->r);
-      }
-    }
-    int64_t off = 0, row0 = 0;
-    for (int32_t b = 0; b < cfg->num_tensors; ++b) {
-      const arc_tensor& t = cfg->tensors[b];
-      const bool aligned = c->d % 4 == 0 && off % 4 == 0 && t.cols % 4 == 0;
-      // Tensors on 16 bytes keep the window kernels, whose launches they
-      // share (per-tensor ResNet-18 377 us, 382 with its rows off the lines
-      // in the span and lines kernels).
-      const int32_t gr = group_rows(aligned, t.cols);
-      const RowKernel kernel = gr == 0   ? RowKernel::kGeneral
-                               : aligned ? RowKernel::kWindow
-                                         : off_line_kernel(t.rows, t.cols, span_r, c->N);
-      add_groups(off, row0, t.rows, t.cols, t.cols, c->v_off[t.cols], kernel, gr, aligned,
-                 &lists);
-      off += t.rows * t.cols;
-      row0 += t.rows;
+      row0 += cfg->tensors[b].rows;
       begin.push_back(row0);
-      want.push_back(t.K);
+      want.push_back(cfg->tensors[b].K);
     }
     build_node_selection(begin, want, c);
-    int64_t agg_off = 0, work = 0;
-    off = 0;
+    int64_t agg_off = 0, work = 0, off = 0;
     for (int32_t b = 0; b < cfg->num_tensors; ++b) {
       const arc_tensor& t = cfg->tensors[b];
       const arc::BucketDesc& bd = c->buckets[b];
@@ -529,6 +553,20 @@ void build_plan(const arc_config* cfg, arc::PlanKind kind, arc_ctx* c) {
   }
   const int64_t nodes = c->compressor == ARC_COMP_TOPK ? c->N : 1;
   c->payload = nodes * c->payload_node;
+  // The first kind of plan that fits, by its number of groups: its tables are
+  // filled only then.
+  c->plan = arc::PlanKind::kFast;
+  if (fits)
+    for (const arc::PlanKind kind : {arc::PlanKind::kFast, arc::PlanKind::kAlignedWindows,
+                                     arc::PlanKind::kGeneral}) {
+      GroupLists counted;
+      counted.count_only = true;
+      plan_rows(cfg, kind, c, &counted);
+      c->plan = kind;
+      if (fits(*c, counted.count)) break;
+    }
+  GroupLists lists;
+  plan_rows(cfg, c->plan, c, &lists);
   c->groups.clear();
   for (int sz = 0; sz < arc::kVecLists; ++sz) {
     c->vec_count[sz] = static_cast<int64_t>(lists.vec[sz].size());
@@ -540,7 +578,7 @@ void build_plan(const arc_config* cfg, arc::PlanKind kind, arc_ctx* c) {
   c->nvec_groups = static_cast<int64_t>(c->groups.size());
   for (const arc::RowGroup& grp : lists.vec[arc::kSpanList]) {
     c->span_floats =
-        std::max(c->span_floats, arc::span_wave_floats(grp.rows, grp.cols, span_r));
+        std::max(c->span_floats, arc::span_wave_floats(grp.rows, grp.cols, span_r(c)));
     c->span_values = std::max(c->span_values, grp.rows * grp.cols);
   }
   c->groups.insert(c->groups.end(), lists.general.begin(), lists.general.end());
@@ -674,7 +712,7 @@ arc_status arc_create(const arc_config* cfg, void* hip_stream, arc_ctx** out) {
 
   arc_ctx* c = new (std::nothrow) arc_ctx();
   if (c == nullptr) return fail(ARC_ERR_NOMEM, "host allocation failed");
-  st = arc::plan_context(cfg, m, hip_stream, arc::PlanKind::kFast, c);
+  st = arc::plan_context(cfg, m, hip_stream, nullptr, c);
   if (st != ARC_OK) {
     delete c;
     return st;
@@ -1229,7 +1267,7 @@ arc_status arc_timing_read(arc_ctx* c, double* ms, int64_t* steps) {
 
 namespace arc {
 
-arc_status plan_context(const arc_config* cfg, int64_t m, void* stream, PlanKind kind,
+arc_status plan_context(const arc_config* cfg, int64_t m, void* stream, const PlanFits& fits,
                         arc_ctx* c) {
   try {
     c->d = cfg->d;
@@ -1244,7 +1282,7 @@ arc_status plan_context(const arc_config* cfg, int64_t m, void* stream, PlanKind
     c->a = 1.0f - cfg->eta;
     c->seed = cfg->seed;
     c->stream = static_cast<hipStream_t>(stream);
-    build_plan(cfg, kind, c);
+    build_plan(cfg, fits, c);
   } catch (...) {
     return fail(ARC_ERR_NOMEM, "host allocation failed");
   }

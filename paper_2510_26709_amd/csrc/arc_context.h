@@ -5,6 +5,7 @@
 #pragma once
 
 #include <array>
+#include <functional>
 #include <map>
 #include <memory>
 #include <string>
@@ -34,6 +35,11 @@ constexpr int kEventsPerStep = 6;
 // it), so the host can queue this many steps minus one ahead of the device
 // before it waits.
 constexpr int kProjectionSlots = 4;
+
+// Which streaming kernels a plan may use: all of them; the window kernels on
+// rows that lie on 16 bytes and the general kernel elsewhere; or the general
+// kernel alone, whose tables are the smallest.
+enum class PlanKind { kFast, kAlignedWindows, kGeneral };
 
 // Record `why` as the calling thread's last error and return s.
 arc_status fail(arc_status s, const std::string& why);
@@ -69,6 +75,7 @@ struct arc_ctx {
   // aligned rows by group size (64, 32, 16, 8 rows: lists 0-3), those with
   // any other rows by group size (lists 4-7), narrow rows (list 8),
   // wide rows off the lines (list 9), then the general ones
+  arc::PlanKind plan = arc::PlanKind::kFast;
   std::vector<arc::RowGroup> groups;
   int64_t nvec_groups = 0;
   std::array<int64_t, arc::kVecLists> vec_count{};  // groups per vectorisable list
@@ -183,16 +190,20 @@ namespace arc {
 // Checks cfg (no HIP call); on success *m_out is the number of rows.
 arc_status check_config(const arc_config* cfg, int64_t* m_out);
 
-// Which streaming kernels a plan may use: all of them; the window kernels on
-// rows that lie on 16 bytes and the general kernel elsewhere; or the general
-// kernel alone, whose tables are the smallest.
-enum class PlanKind { kFast, kAlignedWindows, kGeneral };
+// Whether a plan with that many row groups fits the caller's memory (the
+// context's other tables, its widths and v_floats are set).
+using PlanFits = std::function<bool(const arc_ctx&, int64_t groups)>;
 
 // Fills the context's problem fields and lowers cfg (already checked, m
-// rows) to the kernels' host tables; binds the context to `stream`.  Host
-// work only.
-arc_status plan_context(const arc_config* cfg, int64_t m, void* stream, PlanKind kind,
+// rows) to the kernels' host tables; binds the context to `stream`.  With
+// `fits`, the plan is the first kind that fits, or the smallest.  Host work
+// only.
+arc_status plan_context(const arc_config* cfg, int64_t m, void* stream, const PlanFits& fits,
                         arc_ctx* c);
+
+// Device bytes that arc_step_static needs for a context with that many row
+// groups.
+size_t static_scratch_bytes(const arc_ctx& c, int64_t groups);
 
 // The current device, its LDS limit and the launch shapes that depend on
 // it (no allocation).

@@ -14,7 +14,6 @@
 
 #include <cstring>
 #include <mutex>
-#include <optional>
 #include <vector>
 
 #include "arc_context.h"
@@ -68,7 +67,7 @@ struct Layout {
   size_t S, sigma, sel, state, hist, blockcnt, total;
 };
 
-Layout layout_of(const arc_ctx& c) {
+Layout layout_of(const arc_ctx& c, size_t groups) {
   Layout L{};
   size_t at = 0;
   auto take = [&](size_t bytes) {
@@ -77,7 +76,7 @@ Layout layout_of(const arc_ctx& c) {
     return off;
   };
   const size_t nb = c.buckets.size(), nblk = c.blocks.size();
-  L.groups = take(c.groups.size() * sizeof(arc::RowGroup));
+  L.groups = take(groups * sizeof(arc::RowGroup));
   L.gather = take(c.gather.size() * sizeof(arc::GatherBucket));
   L.buckets = take(nb * sizeof(arc::BucketDesc));
   L.blocks = take(nblk * sizeof(arc::BlockDesc));
@@ -107,6 +106,10 @@ __global__ void __launch_bounds__(256) zero_words_kernel(uint32_t* __restrict__ 
 
 }  // namespace
 
+size_t arc::static_scratch_bytes(const arc_ctx& c, int64_t groups) {
+  return layout_of(c, static_cast<size_t>(groups)).total;
+}
+
 extern "C" arc_status arc_step_static(const arc_config* cfg, void* hip_stream, int64_t t,
                                       const void* grad, float* h, float* g, int32_t* out_idx,
                                       float* out_agg) {
@@ -118,16 +121,15 @@ extern "C" arc_status arc_step_static(const arc_config* cfg, void* hip_stream, i
   // times the row groups of the general ones (5 rows a group instead of 64 at
   // 819 values), so a configuration whose tables do not fit with them is
   // planned with fewer: windows for the aligned rows alone, then none.
-  std::optional<arc_ctx> plan;
-  Layout L{};
-  for (const arc::PlanKind kind : {arc::PlanKind::kFast, arc::PlanKind::kAlignedWindows,
-                                   arc::PlanKind::kGeneral}) {
-    plan.emplace();
-    if ((st = arc::plan_context(cfg, m, hip_stream, kind, &*plan)) != ARC_OK) return st;
-    L = layout_of(*plan);
-    if (L.total <= ARC_STATIC_SCRATCH_BYTES) break;
-  }
-  arc_ctx& c = *plan;
+  arc_ctx c;
+  st = arc::plan_context(
+      cfg, m, hip_stream,
+      [](const arc_ctx& p, int64_t groups) {
+        return arc::static_scratch_bytes(p, groups) <= ARC_STATIC_SCRATCH_BYTES;
+      },
+      &c);
+  if (st != ARC_OK) return st;
+  const Layout L = layout_of(c, c.groups.size());
   if (L.total > ARC_STATIC_SCRATCH_BYTES)
     return arc::fail(ARC_ERR_INVALID,
                      "arc_step_static: this configuration needs " + std::to_string(L.total) +

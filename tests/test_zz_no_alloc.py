@@ -144,3 +144,38 @@ def test_static_step_gpt2s_full_size():
                 assert torch.equal(g_st.view(torch.int32), g_ref.view(torch.int32))
     finally:
         comp.close()
+
+
+# Configurations whose tables fit the static array only with the kernels that
+# need fewer groups (tests/plan_kind_check.cpp has the same sizes): windows for
+# rows on 16 bytes, the general kernel for others, and the general kernel alone
+# where the windows' 8-row groups are too many.  arc_step has no such limit and
+# takes the fastest kernels.
+@pytest.mark.parametrize("n,rows,rest", [(160, 1_800_000, 4), (160, 1_800_000, 1),
+                                         (260, 1_750_000, 0)])
+def test_static_step_with_smaller_tables(n, rows, rest):
+    d = n * rows + rest
+    log(f"[no-alloc] smaller tables n={n} d={d}")
+    dev = torch.device("cuda:0")
+    stream = torch.cuda.current_stream(dev)
+    kw = dict(d=d, N=1, n=n, r=8, K=20_000, eta=0.1, seed=5)
+    comp = arc.Compressor(device=dev, stream=stream, **kw)
+    cfg, keep = arc.make_config(**kw)
+    rng = torch.Generator(device=dev)
+    rng.manual_seed(n + rest)
+    try:
+        grad = torch.randn((1, d), device=dev, generator=rng)
+        h_ref, g_ref = torch.zeros_like(grad), torch.zeros_like(grad)
+        h_st, g_st = torch.zeros_like(grad), torch.zeros_like(grad)
+        idx = torch.empty(comp.K_total, dtype=torch.int32, device=dev)
+        agg = torch.empty(comp.payload, dtype=torch.float32, device=dev)
+        for t in range(2):
+            idx_ref, agg_ref = comp.step(t, grad, h_ref, g_ref)
+            arc.arc_step_static(cfg, stream, t, grad, h_st, g_st, idx, agg)
+            stream.synchronize()
+            assert torch.equal(idx, idx_ref)
+            assert torch.equal(agg.view(torch.int32), agg_ref.reshape(-1).view(torch.int32))
+            assert torch.equal(h_st.view(torch.int32), h_ref.view(torch.int32))
+            assert torch.equal(g_st.view(torch.int32), g_ref.view(torch.int32))
+    finally:
+        comp.close()
