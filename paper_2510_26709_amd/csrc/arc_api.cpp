@@ -216,6 +216,12 @@ struct GroupLists {
   int64_t count = 0;
 };
 
+// Room for `more` groups: large views are not copied as their list grows.
+void grow(std::vector<arc::RowGroup>* list, int64_t more) {
+  const size_t need = list->size() + static_cast<size_t>(more);
+  if (need > list->capacity()) list->reserve(std::max(need, 2 * list->capacity()));
+}
+
 // List of vectorisable groups of that many rows: 16-byte aligned rows, or any.
 int size_slot(int32_t group_rows, bool aligned) {
   return (group_rows == 64 ? 0 : group_rows == 32 ? 1 : group_rows == 16 ? 2 : 3) +
@@ -339,6 +345,7 @@ void add_span_groups(int64_t elem_off, int64_t row0, int64_t rows, int64_t cols,
     out->count += (rows + step - 1) / step;
     return;
   }
+  grow(&out->vec[arc::kSpanList], (rows + step - 1) / step);
   for (int64_t p = 0; p < rows; p += step) {
     arc::RowGroup grp{};
     grp.elem_off = elem_off + p * cols;
@@ -385,11 +392,13 @@ void add_groups(int64_t elem_off, int64_t row0, int64_t rows, int64_t cols, int6
   };
   int64_t p = 0;
   const int32_t S = group_rows > 0 ? row_interleave(cols, group_rows) : 1;
+  const int64_t strided = S > 1 ? rows / (S * step) * S : 0;
+  const int64_t groups = strided + (rows - strided * step + step - 1) / step;
   if (out->count_only) {
-    const int64_t strided = S > 1 ? rows / (S * step) * S : 0;
-    out->count += strided + (rows - strided * step + step - 1) / step;
+    out->count += groups;
     return;
   }
+  grow(&list, groups);
   if (S > 1)
     for (; p + S * step <= rows; p += S * step)
       for (int32_t ph = 0; ph < S; ++ph) push(p + ph, step, S);
@@ -571,16 +580,19 @@ void build_plan(const arc_config* cfg, const arc::PlanFits& fits, arc_ctx* c) {
   for (int sz = 0; sz < arc::kVecLists; ++sz) {
     c->vec_count[sz] = static_cast<int64_t>(lists.vec[sz].size());
     if (sz < arc::kWindowLists) c->vec_occ[sz] = sketch_occupancy(lists.vec[sz], slot_rows(sz));
-    for (const arc::RowGroup& grp : lists.vec[sz])
+    for (const arc::RowGroup& grp : lists.vec[sz]) {
       c->stage_elems[sz] += (grp.rows - 1) * static_cast<int64_t>(grp.cols) + grp.last_len;
-    c->groups.insert(c->groups.end(), lists.vec[sz].begin(), lists.vec[sz].end());
+      if (sz != arc::kSpanList) continue;
+      c->span_floats =
+          std::max(c->span_floats, arc::span_wave_floats(grp.rows, grp.cols, span_r(c)));
+      c->span_values = std::max(c->span_values, grp.rows * grp.cols);
+    }
+    if (c->groups.empty())
+      c->groups = std::move(lists.vec[sz]);
+    else
+      c->groups.insert(c->groups.end(), lists.vec[sz].begin(), lists.vec[sz].end());
   }
   c->nvec_groups = static_cast<int64_t>(c->groups.size());
-  for (const arc::RowGroup& grp : lists.vec[arc::kSpanList]) {
-    c->span_floats =
-        std::max(c->span_floats, arc::span_wave_floats(grp.rows, grp.cols, span_r(c)));
-    c->span_values = std::max(c->span_values, grp.rows * grp.cols);
-  }
   c->groups.insert(c->groups.end(), lists.general.begin(), lists.general.end());
   for (const arc::RowGroup& grp : lists.general)
     c->stage_elems[arc::kVecLists] += (grp.rows - 1) * static_cast<int64_t>(grp.cols) + grp.last_len;

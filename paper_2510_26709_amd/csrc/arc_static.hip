@@ -150,7 +150,8 @@ extern "C" arc_status arc_step_static(const arc_config* cfg, void* hip_stream, i
     ds->pending = false;
   }
   try {
-    ds->staging.assign(L.upload_end, 0);
+    // (What lies between the tables, and V's padding, is never read.)
+    if (ds->staging.size() < L.upload_end) ds->staging.resize(L.upload_end);
   } catch (...) {
     return arc::fail(ARC_ERR_NOMEM, "host allocation failed");
   }
