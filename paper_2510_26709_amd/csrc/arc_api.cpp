@@ -222,12 +222,12 @@ void grow(std::vector<arc::RowGroup>* list, int64_t more) {
   if (need > list->capacity()) list->reserve(std::max(need, 2 * list->capacity()));
 }
 
-// List of vectorisable groups of that many rows: 16-byte aligned rows, or any.
+// List of window groups of that many rows on 16 bytes, or of short rows.
 int size_slot(int32_t group_rows, bool aligned) {
-  return (group_rows == 64 ? 0 : group_rows == 32 ? 1 : group_rows == 16 ? 2 : 3) +
-         (aligned ? 0 : arc::kWindowLists / 2);
+  if (!aligned) return arc::kShortList;
+  return group_rows == 64 ? 0 : group_rows == 32 ? 1 : group_rows == 16 ? 2 : 3;
 }
-int32_t slot_rows(int slot) { return 64 >> slot % (arc::kWindowLists / 2); }
+int32_t slot_rows(int slot) { return slot == arc::kShortList ? 64 : 64 >> slot; }
 
 // Occupancy of one vectorised sketch launch from its groups' mean number of
 // chunks per row (weighted by coordinates).  A wave streams one chunk while
@@ -924,7 +924,7 @@ arc_status launch_streaming_stage(arc_ctx* c, const void* grad, float* h, const 
         continue;
       }
       const int32_t gr = slot_rows(w);
-      const bool unaligned = !aligned || w >= arc::kWindowLists / 2;
+      const bool unaligned = !aligned || w == arc::kShortList;
       if (norm) {
         ARC_HIP(arc::launch_row_norms(gr, unaligned, grad, c->grad_bf16, h, g, c->V_dev, grp,
                                       c->vec_count[w], c->S_dev, c->d, c->m, c->N, c->eta, c->a,
@@ -1170,14 +1170,16 @@ arc_status arc_describe(const arc_ctx* c, char* buf, int64_t len) {
   for (const auto& b : c->buckets) radix += b.mode == arc::kSelectRadix;
   long long strided = 0;
   for (const auto& grp : c->groups) strided += grp.stride > 1;
-  // Group counts and launch shapes by group size, aligned rows and others.
-  long long count[4], unaligned = 0;
+  // Group counts and launch shapes by group size, short rows with the 64-row groups.
+  long long count[4];
   arc::SketchOccupancy occ[4];
   for (int sz = 0; sz < 4; ++sz) {
-    count[sz] = c->vec_count[sz] + c->vec_count[4 + sz];
-    occ[sz] = c->vec_occ[c->vec_count[sz] > 0 || c->vec_count[4 + sz] == 0 ? sz : 4 + sz];
-    unaligned += c->vec_count[4 + sz];
+    count[sz] = c->vec_count[sz];
+    occ[sz] = c->vec_occ[sz];
   }
+  const long long unaligned = c->vec_count[arc::kShortList];
+  if (unaligned > 0 && count[0] == 0) occ[0] = c->vec_occ[arc::kShortList];
+  count[0] += unaligned;
   std::snprintf(buf, static_cast<size_t>(len),
                 "compressor=%s mode=%s sketch=%s widths=%zu row_groups=%lld vector_groups=%lld "
                 "(64:%lld 32:%lld 16:%lld 8:%lld rows) workgroup_waves=(%d%s %d%s %d%s %d%s) "

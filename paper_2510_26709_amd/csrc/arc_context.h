@@ -19,10 +19,11 @@
 
 namespace arc {
 
-// Lists of vectorisable row groups: four group sizes, aligned and unaligned,
-// for the column-window kernels, then the groups of narrow rows and of wide
-// rows off the lines.
-constexpr int kWindowLists = 8;
+// Lists of vectorisable row groups: for the column-window kernels four group
+// sizes of rows on 16 bytes, then 64-row groups of rows of one to three values;
+// then the groups of narrow rows and of wide rows off the lines.
+constexpr int kShortList = 4;
+constexpr int kWindowLists = kShortList + 1;
 constexpr int kSpanList = kWindowLists;
 constexpr int kLinesList = kWindowLists + 1;
 constexpr int kVecLists = kWindowLists + 2;
@@ -72,9 +73,9 @@ struct arc_ctx {
   std::map<int64_t, int64_t> v_off;
   int64_t v_floats = 0;
   // row groups, one list per launch: the vectorisable ones with 16-byte
-  // aligned rows by group size (64, 32, 16, 8 rows: lists 0-3), those with
-  // any other rows by group size (lists 4-7), narrow rows (list 8),
-  // wide rows off the lines (list 9), then the general ones
+  // aligned rows by group size (64, 32, 16, 8 rows: lists 0-3), rows of one to
+  // three values (list 4), narrow rows (list 5), wide rows off the lines (list
+  // 6), then the general ones
   arc::PlanKind plan = arc::PlanKind::kFast;
   std::vector<arc::RowGroup> groups;
   int64_t nvec_groups = 0;

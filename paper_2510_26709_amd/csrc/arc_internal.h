@@ -128,9 +128,9 @@ struct SketchOccupancy {
 
 // Momentum + residual + per-worker sketch into S for the row groups
 // groups[0 .. ngroups), any N.  Every group must be vectorisable for
-// group_rows in {64, 32, 16, 8}: at most group_rows rows, cols at most 2^22,
-// r in {1, 2, 4, 8}; without `unaligned`, also cols a multiple of 4 and
-// 16-byte aligned rows.
+// group_rows in {64, 32, 16, 8}: at most group_rows rows, cols a multiple of 4
+// and at most 2^22, r in {1, 2, 4, 8}, rows on 16 bytes; with `unaligned`, rows
+// anywhere, and in 64-row groups also of one to three values.
 hipError_t launch_sketch_per_worker(int32_t group_rows, bool unaligned, const void* grad, int32_t grad_bf16,
                                     float* h, const float* g, const float* V,
                                     const RowGroup* groups, int64_t ngroups, float* S,

@@ -56,7 +56,11 @@ constexpr int slice_f4() {
                                : slice_src_f4<R, G, NORM>();
 }
 // Unaligned rows keep the Delta of their last n % 4 columns after the slice,
-// one float4 per row.
+// one float4 per row.  (Plans send rows of one to three values here, in 64-row
+// groups, and others of a multiple of four values; with those columns' code and
+// LDS taken out of the forms that have none, arrays off 16 bytes took 3-6%
+// longer: 4 workers, 8.0e7 bf16 values of 256 a row 244 -> 256-260 us a step, of
+// 64 a row 249 -> 258-260, whichever of the two was left in.)
 template <int R, int G, bool NORM, bool UNAL>
 constexpr int wave_lds_f4() { return kTileF4 + slice_f4<R, G, NORM>() + (UNAL ? G : 0); }
 // Offset whose access the hardware drops: a group spans at most 2^30 bytes
@@ -80,19 +84,16 @@ constexpr uint32_t kDropOffset = 0x80000000u;
 // rows read as zero and are not stored.
 // Lanes G..63 repeat the chains of lanes 0..G-1; the caller keeps only lanes
 // below the group's row count.
-// UNAL: rows may start and end anywhere (an odd width, a worker base or a
-// tensor at an odd coordinate, pointers off 16 bytes).  16-byte accesses need
-// only whole words, so binary32 rows are streamed as they lie; a bf16 row
+// UNAL: rows may start and end anywhere.  Taken by layouts planned for 16-byte
+// rows whose arrays are off 16 bytes, and by rows of one to three values; other
+// rows off the lines have kernels of their own (arc_span.hip, arc_lines.hip).
+// 16-byte accesses need only whole words, so binary32 rows are streamed as they lie; a bf16 row
 // that starts in the upper half of a word is read as the two or three words
 // that hold each quad and shifted into place; the last n % 4 columns of every
 // row are taken one value per lane, loaded before the first chunk and chained
-// after the last.  Taken by layouts planned for 16-byte rows whose arrays are
-// off 16 bytes, and by rows of one to three values; other rows off the lines
-// have kernels of their own (arc_span.hip, arc_lines.hip).  Bound by HBM like
-// the aligned kernel, less the lines that two accesses share: 2.0e7 binary32
-// values of 3001 a row, 4 workers, 0.316 ms a step, where one value per lane
-// throughout, as such rows once took, is 4-5 times slower (per-tensor CIFAR
-// ResNet-18 1.266 ms, 0.309 through this kernel).
+// after the last.  Bound by HBM like the aligned kernel, less the lines that two
+// accesses share.  8.0e7 binary32 values of one worker, 1 / 2 / 3 a row, 1.93 /
+// 1.10 / 0.81 ms a step (the general kernel 4.62 / 2.46 / 1.77).
 // NORM (R = 1): the chain is the row's squared
 // norm, fmaf(Delta, Delta, s), and V is unused.
 template <int R, bool BF16, int G, bool NORM, bool UNAL>
