@@ -598,13 +598,15 @@ void build_plan(const arc_config* cfg, const arc::PlanFits& fits, arc_ctx* c) {
     c->stage_elems[arc::kVecLists] += (grp.rows - 1) * static_cast<int64_t>(grp.cols) + grp.last_len;
 }
 
-// Values of the smaller streaming launches, over all workers, from which on they
-// run beside the largest on a second stream instead of before it.  The fork and
-// join cost up to 37 us where the launches are short (step us, forked / in
-// turn: 100 rows of 33 values and a row of 100 62 / 23; GPT-2 layouts of hidden
-// size 64 to 256, 2.8e5 to 1.9e7 values in all 57 / 27 to 118 / 115; CIFAR
-// ResNet-18, 4 workers, 4.5e7 values 273 / 270, 8 workers 493 / 499).
-constexpr int64_t kForkElems = 30'000'000;
+// Values of a layout, over all workers, from which on its smaller streaming
+// launches run beside the largest on a second stream instead of before it.  The
+// fork and join cost up to 37 us where the launches are short (step us, forked /
+// in turn: 100 rows of 33 values and a row of 100 62 / 23; GPT-2 layouts of
+// hidden size 64 to 256, 2.8e5 to 1.9e7 values in all 57 / 27 to 118 / 115; CIFAR
+// ResNet-18 of width 48, 8 workers, 5.0e7 values 304 / 289) and are hidden where
+// the largest is long (ResNet-18, 8 workers, 9.4e7 values 382 / 386; CIFAR
+// ResNet-18, 8.9e7 493 / 499).
+constexpr int64_t kForkElems = 80'000'000;
 
 template <typename T>
 arc_status dev_alloc(T** p, size_t count, const char* what) {
@@ -783,12 +785,9 @@ arc_status arc_create(const arc_config* cfg, void* hip_stream, arc_ctx** out) {
     }
   }
   {
-    int64_t all = 0, big = 0;
-    for (const int64_t elems : c->stage_elems) {
-      all += elems;
-      big = std::max(big, elems);
-    }
-    if ((all - big) * c->N >= kForkElems) {
+    int launches = 0;
+    for (const int64_t elems : c->stage_elems) launches += elems > 0;
+    if (launches > 1 && c->d * c->N >= kForkElems) {
       e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking);
       for (int k = 0; k < arc::kProjectionSlots && e == hipSuccess; ++k) {
         e = hipEventCreateWithFlags(&c->fork_ev[k], hipEventDisableTiming);
