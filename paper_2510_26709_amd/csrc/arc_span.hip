@@ -29,13 +29,14 @@ constexpr uint32_t kDropOffset = 0x80000000u;  // beyond every resource here
 // stay under half a SIMD's (two waves): at 258 instead of 233 the rows of 333
 // values took 330 us instead of 303.  Short spans hold fewer loads and run more
 // waves (LOADS, see span_loads).
-// Step times (us), 4 workers of 2.0e7 values (8 of 1.2e7 for ResNet-18), the
-// window kernels / this one: 512-wide rows 32 bytes further off a line from
-// worker to worker (ResNet-18) 322 / 301; binary32 rows of 333 values 370 /
-// 301, 600 321 / 284, 800 531 / 269, 77 (1.0e7) 246 / 182; bf16 rows of 640
-// at an odd base 280 / 227, of 681 285 / 247.  Rows on the lines stay with
-// the window kernels (512: 284 / 295, 768: 261 / 338), and rows too wide for
-// five to fit a span go to the lines kernel (1001: 266 / 295 before that).
+// Step times (us), r = 4, the window kernels / this one.  4 workers of 2.0e7 + x
+// binary32 values, so that each worker's base lies x values further past a line
+// than the one before: rows of 100 values (x = 4) 413 / 267, 300 (8) 337 / 268,
+// 512 (8) 280 / 270, 600 (4) 315 / 273, 640 (8) 281 / 265, 704 (8) 392 / 267; bf16
+// 100 (8) 334 / 217, 512 (8) 236 / 220, 640 (8) 230 / 215.  ResNet-18 (8 workers
+// of 1.2e7, 512-wide rows, x = 8) 322 / 301.  On the lines (x = 0) 512 258 / 269,
+// 768 262 / 266, which keep the windows, as do the widths at odd multiples of 32
+// and 64 that are slower there (704 273 / 262, 800 304 / 265).
 template <int R, bool BF16, bool NORM, int LOADS>
 __global__ void __launch_bounds__(kWave, LOADS == kMaxSpanLoads ? 2 : 4)
 sketch_span_kernel(const void* __restrict__ grad, float* __restrict__ h,
