@@ -580,7 +580,11 @@ void build_plan(const arc_config* cfg, const arc::PlanFits& fits, arc_ctx* c) {
   for (int sz = 0; sz < arc::kVecLists; ++sz) {
     c->vec_count[sz] = static_cast<int64_t>(lists.vec[sz].size());
     if (sz < arc::kWindowLists) c->vec_occ[sz] = sketch_occupancy(lists.vec[sz], slot_rows(sz));
+    const int64_t cw = sz < arc::kWindowLists ? arc::vector_chunk_cols(slot_rows(sz))
+                       : sz == arc::kSpanList ? arc::kSpanValues
+                                              : arc::vector_chunk_cols(arc::kLineRows);
     for (const arc::RowGroup& grp : lists.vec[sz]) {
+      c->stage_steps[sz] = std::max(c->stage_steps[sz], (grp.cols + cw - 1) / cw);
       c->stage_elems[sz] += (grp.rows - 1) * static_cast<int64_t>(grp.cols) + grp.last_len;
       if (sz != arc::kSpanList) continue;
       c->span_floats =
@@ -594,19 +598,38 @@ void build_plan(const arc_config* cfg, const arc::PlanFits& fits, arc_ctx* c) {
   }
   c->nvec_groups = static_cast<int64_t>(c->groups.size());
   c->groups.insert(c->groups.end(), lists.general.begin(), lists.general.end());
-  for (const arc::RowGroup& grp : lists.general)
+  for (const arc::RowGroup& grp : lists.general) {
+    // (32 columns at a time, four passes of 16 rows each.)
+    c->stage_steps[arc::kVecLists] =
+        std::max<int64_t>(c->stage_steps[arc::kVecLists], (grp.cols + 31) / 32);
     c->stage_elems[arc::kVecLists] += (grp.rows - 1) * static_cast<int64_t>(grp.cols) + grp.last_len;
+  }
 }
 
-// Values of a layout, over all workers, from which on its smaller streaming
-// launches run beside the largest on a second stream instead of before it.  The
-// fork and join cost up to 37 us where the launches are short (step us, forked /
-// in turn: 100 rows of 33 values and a row of 100 62 / 23; GPT-2 layouts of
-// hidden size 64 to 256, 2.8e5 to 1.9e7 values in all 57 / 27 to 118 / 115; CIFAR
-// ResNet-18 of width 48, 8 workers, 5.0e7 values 304 / 289) and are hidden where
-// the largest is long (ResNet-18, 8 workers, 9.4e7 values 382 / 386; CIFAR
-// ResNet-18, 8.9e7 493 / 499).
-constexpr int64_t kForkElems = 80'000'000;
+// Whether a layout's smaller streaming launches run beside the largest on a
+// second stream instead of before it.  The fork and join cost up to 37 us where
+// the launches are short (step us, forked / in turn: 100 rows of 33 values and a
+// row of 100 62 / 23; GPT-2 layouts of hidden size 64 to 256, 2.8e5 to 1.9e7
+// values in all 57 / 27 to 118 / 115; CIFAR ResNet-18 of width 48, 8 workers,
+// 5.0e7 values 304 / 289), and are hidden where the largest is long (ResNet-18, 8
+// workers, 9.4e7 values 382 / 386; GPT-2, 7.8e7 274 / 282).  A launch of a few
+// groups with many chunks a row takes long however few its values are, and is
+// better hidden beside the largest (Llama layouts with 24 and 70 groups of 64-row
+// groups of some 60 chunks, 2.8e7 and 5.2e7 values: 153 / 168 and 221 / 250;
+// ResNet-18 of odd width 236 / 325; GPT-2 with rows of 7 chunks 112 / 116).
+constexpr int64_t kForkElems = 60'000'000;
+constexpr int64_t kForkSteps = 6;
+bool fork_pays(const arc_ctx* c) {
+  int launches = 0;
+  int64_t steps = 0;
+  size_t big = 0;
+  for (size_t l = 0; l < c->stage_elems.size(); ++l) {
+    launches += c->stage_elems[l] > 0;
+    steps += c->stage_steps[l];
+    if (c->stage_elems[l] > c->stage_elems[big]) big = l;
+  }
+  return launches > 1 && (c->d * c->N >= kForkElems || steps - c->stage_steps[big] > kForkSteps);
+}
 
 template <typename T>
 arc_status dev_alloc(T** p, size_t count, const char* what) {
@@ -785,9 +808,7 @@ arc_status arc_create(const arc_config* cfg, void* hip_stream, arc_ctx** out) {
     }
   }
   {
-    int launches = 0;
-    for (const int64_t elems : c->stage_elems) launches += elems > 0;
-    if (launches > 1 && c->d * c->N >= kForkElems) {
+    if (fork_pays(c)) {
       e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking);
       for (int k = 0; k < arc::kProjectionSlots && e == hipSuccess; ++k) {
         e = hipEventCreateWithFlags(&c->fork_ev[k], hipEventDisableTiming);
@@ -869,7 +890,7 @@ namespace {
 
 // The streaming stage (S1-S3; norm: Top-K's row norms): one launch per
 // non-empty list of row groups, in turn on the caller's stream, or, where the
-// context holds a second stream (kForkElems), the one over the most coordinates
+// context holds a second stream (fork_pays), the one over the most coordinates
 // on the caller's stream and the others on the second one, forked after everything queued before and joined before anything
 // queued after, so that they overlap it instead of following it.  Without
 // `aligned` (grad, h and g on 16 bytes) the lists of aligned rows take the

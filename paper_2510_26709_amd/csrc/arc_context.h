@@ -81,6 +81,7 @@ struct arc_ctx {
   int64_t nvec_groups = 0;
   std::array<int64_t, arc::kVecLists> vec_count{};  // groups per vectorisable list
   std::array<int64_t, arc::kVecLists + 1> stage_elems{};  // coordinates per list, general last
+  std::array<int64_t, arc::kVecLists + 1> stage_steps{};  // most chunks of a row per list
   std::array<arc::SketchOccupancy, arc::kWindowLists> vec_occ{};  // launch shapes
   // LDS floats and most values of a wave of the narrow rows' launch
   int32_t span_floats = 0, span_values = 0;

@@ -182,17 +182,23 @@ def test_single_view_equals_per_tensor_with_one_tensor():
     assert h0.tobytes() == h1.tobytes() and g0.tobytes() == g1.tobytes()
 
 
-# Several streaming launches: in turn in small layouts, on the second stream from
-# 8.0e7 values (all workers) on.
-@pytest.mark.parametrize("N,forked", [(1, 0), (38, 0), (39, 1)])
-def test_short_launches_are_not_forked(N, forked):
-    tensors = [(330, 3333, 2), (140_000, 7, 3), (7, 5, 1)]
-    total = sum(a * b for a, b, _ in tensors)
-    assert 38 * total < 80_000_000 <= 39 * total
+# Several streaming launches: in turn while the layout is small and the smaller
+# launches short, on the second stream from 6.0e7 values (all workers) or more
+# than six chunks of them on (64-row groups of 33, five and seven chunks).
+NARROW = [(330, 3333, 2), (140_000, 7, 3), (7, 5, 1)]
+
+
+@pytest.mark.parametrize("tensors,N,forked", [
+    (NARROW, 1, 0), (NARROW, 28, 0), (NARROW, 29, 1),
+    ([(4000, 256, 3), (64, 1056, 2)], 2, 1), ([(4000, 256, 3), (64, 160, 2)], 2, 0),
+    ([(4000, 256, 3), (64, 224, 2)], 2, 1)])
+def test_short_launches_are_not_forked(tensors, N, forked):
+    total = sum(a * b for a, b, _ in NARROW)
+    assert 28 * total < 60_000_000 <= 29 * total
     d = sum(a * b for a, b, _ in tensors)
     comp = arc.Compressor(d=d, N=N, r=4, tensors=tensors, eta=0.1, seed=1)
     try:
         assert f"forked={forked} " in comp.describe(), comp.describe()
     finally:
         comp.close()
-    run_case(label=f"forked_{N}", d=d, N=N, tensors=tensors, steps=3, check_S=True)
+    run_case(label=f"forked_{N}_{forked}", d=d, N=N, tensors=tensors, steps=3, check_S=True)
